@@ -1,0 +1,240 @@
+// Register/LDS 2D FFT of one workgroup over an H x W complex field (H = RC RD,
+// W = RA RB), V values per thread, whose Fourier-space end leaves every mode k
+// in the same thread as its mirror -k.  Passes and exchanges as in
+// mf_resident_fft.hpp:
+//   rows    x = x0 + RB m,  kx = k1 + RA k2  (pass A: radix-RA over m, pass B: radix-RB over x0)
+//   columns y = y0 + RD m,  ky = k1 + RC k2  (pass C: radix-RC over m, pass D: radix-RD over y0)
+// E1 rows have bases that keep pass A's and pass B's accesses on distinct
+// banks, E2 and E3 have pitch W + 1, and the exchanges A -> A, C -> C and
+// D -> D rewrite the addresses a thread has just read (no barrier).
+//
+// A pass-D task (kx, k1) is one radix-RD butterfly and holds the modes (k1 +
+// RC k2, kx), k2 < RD; the modes -k of it are those of the task (-kx, -k1).  A
+// thread takes a task and its mirror (V = 2 RD), so that a Fourier step that
+// combines Z(k) with Z(-k) needs no exchange.  Four tasks (kx in {0, W/2}, k1
+// in {0, RC/2}) are their own mirrors; two threads take two of them each.
+#pragma once
+#include "mf_device.hpp"
+#include "mf_resident_fft.hpp"
+
+namespace mf {
+
+namespace {
+
+template <int H_, int W_, int V_, int RA_, int RB_, int RC_, int RD_>
+struct Rect {
+    static constexpr int H = H_, W = W_, V = V_, RA = RA_, RB = RB_, RC = RC_, RD = RD_;
+    static_assert(H == RC * RD && W == RA * RB && V == 2 * RD, "Rect shape");
+    static constexpr int NT = H * W / V;    // threads per workgroup
+    static constexpr int TA = V / RA;       // tasks per thread in passes A (1 or 2), B and C
+    static constexpr int TB = V / RB;
+    static constexpr int TC = V / RC;
+    static constexpr int R1 = 32 / RB;
+    static constexpr int YC = H / V;        // step of pass C's y0 between a thread's tasks
+    static_assert(TA <= 2 && TB >= 1 && TC >= 1 && NT % W == 0, "Rect shape");
+    static constexpr int e1_base(int r) { return r * W + 2 * ((RB / 2) * (r % R1) + (r / R1) % (RB / 2)) + 32 * (r / R1); }
+    static constexpr int extent() {
+        int m = H * (W + 1);
+        for (int r = 0; r < H; ++r) m = e1_base(r) + W > m ? e1_base(r) + W : m;
+        return m;
+    }
+    static constexpr int LDS = extent();    // float2 elements of the exchange buffer
+    // twiddle tables: A [x0 < RB][k1 < RA] pitch RA + 1, B [k1 < RA][x0 < RB],
+    // C [y0 < RD][k1 < RC], D [k1 < RC][y0 < RD] pitch RD + 1
+    static constexpr int TWA = 0, TWB = TWA + (RA + 1) * RB, TWC = TWB + RA * RB, TWD = TWC + RD * RC;
+    static constexpr int TWS = TWD + (RD + 1) * RC;
+};
+
+// The tasks of a thread in pass D.
+struct DPair {
+    unsigned kxa, k1a, kxb, k1b;
+    bool self;  // each task is its own mirror (else each is the other's)
+    bool zero;  // k1a = 0: mode k2 mirrors (RD - k2) mod RD, else RD - 1 - k2
+};
+template <typename S>
+__device__ __forceinline__ DPair d_pair(unsigned tid) {
+    constexpr unsigned W = S::W, RC = S::RC;
+    const unsigned kx = tid % (W / 2), k1 = tid / (W / 2);
+    DPair p;
+    p.self = kx == 0 && (k1 == 0 || k1 == RC / 2);
+    p.zero = k1 == 0;
+    p.kxa = kx == 0 && k1 > RC / 2 ? W / 2 : kx;
+    p.k1a = k1;
+    p.kxb = p.self ? W / 2 : (W - p.kxa) % W;
+    p.k1b = p.self ? k1 : (RC - k1) % RC;
+    return p;
+}
+
+// Fill the twiddle tables from twr[r] = W_W^r and twc[r * sc] = W_H^r.
+template <typename S>
+__device__ __forceinline__ void rect_twiddles(float2* t, const float2* __restrict__ twr,
+                                              const float2* __restrict__ twc, int sc, unsigned tid) {
+    for (unsigned e = tid; e < (unsigned)S::TWS; e += S::NT) {
+        if (e < (unsigned)S::TWB) {
+            const unsigned a = e / (S::RA + 1), b = e % (S::RA + 1);
+            t[e] = twr[b < (unsigned)S::RA ? a * b : 0];
+        } else if (e < (unsigned)S::TWC) {
+            const unsigned q = e - S::TWB;
+            t[e] = twr[(q / S::RB) * (q % S::RB)];
+        } else if (e < (unsigned)S::TWD) {
+            const unsigned q = e - S::TWC;
+            t[e] = twc[(q / S::RC) * (q % S::RC) * sc];
+        } else {
+            const unsigned q = e - S::TWD, a = q / (S::RD + 1), b = q % (S::RD + 1);
+            t[e] = twc[b < (unsigned)S::RD ? a * b * sc : 0];
+        }
+    }
+}
+
+template <typename S>
+__device__ __forceinline__ unsigned rect_e1(unsigned r, unsigned c) {
+    return r * S::W + 2 * ((S::RB / 2) * (r % S::R1) + (r / S::R1) % (S::RB / 2)) + 32 * (r / S::R1) + c;
+}
+template <typename S>
+__device__ __forceinline__ unsigned rect_e2(unsigned r, unsigned c) {
+    return r * (S::W + 1) + c;
+}
+
+// Thread coordinates in each layout (tid in [0, NT)):
+//   A: y = tid / (RB/TA), j = tid % (RB/TA); holds x = TA j + q + RB m  at v[RA q + m]
+//   B: t = tid + i NT (i < TB): y = t % H, k1 = t / H; holds x0         at v[RB i + x0]
+//   C: kx = tid % W, y0 = tid / W + i YC (i < TC); holds m              at v[RC i + m]
+//   D: DPair; task a's modes (k1a + RC k2, kxa) at v[k2], task b's at v[RD + k2]
+template <typename S>
+__device__ __forceinline__ void store_e1_a(float2* lds, const float2 (&v)[S::V], unsigned y, unsigned j) {
+#pragma unroll
+    for (int k = 0; k < S::RA; ++k) {
+        if constexpr (S::TA == 2) st2(lds, rect_e1<S>(y, k * S::RB + 2 * j), v[k], v[S::RA + k]);
+        else lds[rect_e1<S>(y, k * S::RB + j)] = v[k];
+    }
+}
+template <typename S>
+__device__ __forceinline__ void load_e1_a(const float2* lds, float2 (&v)[S::V], unsigned y, unsigned j) {
+#pragma unroll
+    for (int k = 0; k < S::RA; ++k) {
+        if constexpr (S::TA == 2) ld2(lds, rect_e1<S>(y, k * S::RB + 2 * j), v[k], v[S::RA + k]);
+        else v[k] = lds[rect_e1<S>(y, k * S::RB + j)];
+    }
+}
+
+template <typename S>
+__device__ __forceinline__ void rect_forward(float2 (&v)[S::V], float2* lds, const float2* __restrict__ tw,
+                                             unsigned tid, const DPair& dp) {
+    constexpr int RA = S::RA, RB = S::RB, RC = S::RC, RD = S::RD, H = S::H;
+    const unsigned ya = tid / (RB / S::TA), j = tid % (RB / S::TA);
+    // A
+#pragma unroll
+    for (int q = 0; q < S::TA; ++q) {
+        dft_slice<RA, false>(v + RA * q);
+        const float2* row = tw + S::TWA + (RA + 1) * (S::TA * j + q);
+#pragma unroll
+        for (int k = 1; k < RA; ++k) v[RA * q + k] = twiddle<false>(v[RA * q + k], row, k);
+    }
+    store_e1_a<S>(lds, v, ya, j);
+    __syncthreads();
+    // B
+#pragma unroll
+    for (int i = 0; i < S::TB; ++i) {
+        const unsigned t = tid + i * S::NT, y = t % H, k1 = t / H;
+#pragma unroll
+        for (int x = 0; x < RB; x += 2) ld2(lds, rect_e1<S>(y, k1 * RB + x), v[RB * i + x], v[RB * i + x + 1]);
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < S::TB; ++i) dft_slice<RB, false>(v + RB * i);
+#pragma unroll
+    for (int i = 0; i < S::TB; ++i) {
+        const unsigned t = tid + i * S::NT, y = t % H, k1 = t / H;
+#pragma unroll
+        for (int k = 0; k < RB; ++k) lds[rect_e2<S>(y, k1 + RA * k)] = v[RB * i + k];
+    }
+    __syncthreads();
+    // C
+    const unsigned kx = tid % S::W, yc = tid / S::W;
+#pragma unroll
+    for (int i = 0; i < S::TC; ++i)
+#pragma unroll
+        for (int m = 0; m < RC; ++m) v[RC * i + m] = lds[rect_e2<S>(yc + i * S::YC + RD * m, kx)];
+#pragma unroll
+    for (int i = 0; i < S::TC; ++i) {
+        dft_slice<RC, false>(v + RC * i);
+        const float2* row = tw + S::TWC + RC * (yc + i * S::YC);
+#pragma unroll
+        for (int k = 1; k < RC; ++k) v[RC * i + k] = twiddle<false>(v[RC * i + k], row, k);
+#pragma unroll
+        for (int k = 0; k < RC; ++k) lds[rect_e2<S>(RD * k + yc + i * S::YC, kx)] = v[RC * i + k];
+    }
+    __syncthreads();
+    // D
+#pragma unroll
+    for (int y = 0; y < RD; ++y) {
+        v[y] = lds[rect_e2<S>(RD * dp.k1a + y, dp.kxa)];
+        v[RD + y] = lds[rect_e2<S>(RD * dp.k1b + y, dp.kxb)];
+    }
+    dft_slice<RD, false>(v);
+    dft_slice<RD, false>(v + RD);
+}
+
+template <typename S>
+__device__ __forceinline__ void rect_inverse(float2 (&v)[S::V], float2* lds, const float2* __restrict__ tw,
+                                             unsigned tid, const DPair& dp) {
+    constexpr int RA = S::RA, RB = S::RB, RC = S::RC, RD = S::RD, H = S::H;
+    // D
+    dft_slice<RD, true>(v);
+    dft_slice<RD, true>(v + RD);
+    {
+        const float2* ra = tw + S::TWD + (RD + 1) * dp.k1a;
+        const float2* rb = tw + S::TWD + (RD + 1) * dp.k1b;
+#pragma unroll
+        for (int y = 1; y < RD; ++y) {
+            v[y] = twiddle<true>(v[y], ra, y);
+            v[RD + y] = twiddle<true>(v[RD + y], rb, y);
+        }
+    }
+#pragma unroll
+    for (int y = 0; y < RD; ++y) {
+        lds[rect_e2<S>(RD * dp.k1a + y, dp.kxa)] = v[y];
+        lds[rect_e2<S>(RD * dp.k1b + y, dp.kxb)] = v[RD + y];
+    }
+    __syncthreads();
+    // C
+    const unsigned kx = tid % S::W, yc = tid / S::W;
+#pragma unroll
+    for (int i = 0; i < S::TC; ++i)
+#pragma unroll
+        for (int k = 0; k < RC; ++k) v[RC * i + k] = lds[rect_e2<S>(RD * k + yc + i * S::YC, kx)];
+#pragma unroll
+    for (int i = 0; i < S::TC; ++i) {
+        dft_slice<RC, true>(v + RC * i);
+#pragma unroll
+        for (int m = 0; m < RC; ++m) lds[rect_e2<S>(yc + i * S::YC + RD * m, kx)] = v[RC * i + m];
+    }
+    __syncthreads();
+    // B
+#pragma unroll
+    for (int i = 0; i < S::TB; ++i) {
+        const unsigned t = tid + i * S::NT, y = t % H, k1 = t / H;
+#pragma unroll
+        for (int k = 0; k < RB; ++k) v[RB * i + k] = lds[rect_e2<S>(y, k1 + RA * k)];
+    }
+    __syncthreads();
+#pragma unroll
+    for (int i = 0; i < S::TB; ++i) {
+        const unsigned t = tid + i * S::NT, y = t % H, k1 = t / H;
+        dft_slice<RB, true>(v + RB * i);
+        const float2* row = tw + S::TWB + RB * k1;
+#pragma unroll
+        for (int x = 1; x < RB; ++x) v[RB * i + x] = twiddle<true>(v[RB * i + x], row, x);
+#pragma unroll
+        for (int x = 0; x < RB; x += 2) st2(lds, rect_e1<S>(y, k1 * RB + x), v[RB * i + x], v[RB * i + x + 1]);
+    }
+    __syncthreads();
+    // A
+    load_e1_a<S>(lds, v, tid / (RB / S::TA), tid % (RB / S::TA));
+#pragma unroll
+    for (int q = 0; q < S::TA; ++q) dft_slice<RA, true>(v + RA * q);
+}
+
+}  // namespace
+
+}  // namespace mf
