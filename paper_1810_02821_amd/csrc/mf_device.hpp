@@ -322,12 +322,27 @@ __device__ __forceinline__ Philox4 philox4x32_10(uint32_t c0, uint32_t c1, uint3
 }
 
 // Box-Muller on the top 24 bits of two words: u1 in (0, 1], u2 in [0, 1),
-// both exact in FP32.  v_log_f32 is log2 and v_sin/v_cos take revolutions.
+// both exact in FP32 (u1 = (x >> 8) 2^-24 + 2^-24 in one exact FMA).
+// v_log_f32 is log2 and v_sin/v_cos take revolutions.
+__device__ __forceinline__ float bm_u1(uint32_t xa) { return fmaf((float)(xa & 0xFFFFFF00u), 0x1p-32f, 0x1p-24f); }
+__device__ __forceinline__ float bm_u2(uint32_t xb) { return (float)(xb >> 8) * 0x1p-24f; }
 __device__ __forceinline__ float2 box_muller(uint32_t xa, uint32_t xb) {
-    const float u1 = (float)((xa >> 8) + 1u) * 0x1p-24f;
-    const float u2 = (float)(xb >> 8) * 0x1p-24f;
-    const float r = __builtin_amdgcn_sqrtf(-1.3862943611198906f * __builtin_amdgcn_logf(u1));
+    const float u2 = bm_u2(xb);
+    const float r = __builtin_amdgcn_sqrtf(-1.3862943611198906f * __builtin_amdgcn_logf(bm_u1(xa)));
     return make_float2(r * __builtin_amdgcn_cosf(u2), r * __builtin_amdgcn_sinf(u2));
+}
+// The same pair of normals as kBoxMuller r (c, s): a caller folds kBoxMuller =
+// sqrt(2 ln 2) into the standard deviation sd and takes (sd r) c and (sd r) s,
+// two multiplications fewer per pair.
+constexpr float kBoxMuller = 1.1774100225154747f;
+constexpr float kBoxMuller2 = 1.3862943611198906f;  // its square
+struct Polar {
+    float r, c, s;
+};
+__device__ __forceinline__ Polar polar(uint32_t xa, uint32_t xb) {
+    const float u2 = bm_u2(xb);
+    return {__builtin_amdgcn_sqrtf(-__builtin_amdgcn_logf(bm_u1(xa))), __builtin_amdgcn_cosf(u2),
+            __builtin_amdgcn_sinf(u2)};
 }
 
 enum : uint32_t { kStagePixel = 0, kStageHarmonic = 1, kStageInit = 2 };
@@ -341,6 +356,14 @@ __device__ __forceinline__ Normals2 pair_normals(uint32_t j, uint32_t sweep, uin
                                                  uint32_t pair, uint32_t k0, uint32_t k1) {
     const Philox4 r = philox4x32_10(j, sweep, (prob << 8) | stage, pair, k0, k1);
     return {box_muller(r.x, r.y), box_muller(r.z, r.w)};
+}
+struct Polar2 {
+    Polar a, b;
+};
+__device__ __forceinline__ Polar2 pair_polar(uint32_t j, uint32_t sweep, uint32_t prob, uint32_t stage, uint32_t pair,
+                                             uint32_t k0, uint32_t k1) {
+    const Philox4 r = philox4x32_10(j, sweep, (prob << 8) | stage, pair, k0, k1);
+    return {polar(r.x, r.y), polar(r.z, r.w)};
 }
 
 }  // namespace mf

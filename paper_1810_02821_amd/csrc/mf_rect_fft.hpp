@@ -235,6 +235,65 @@ __device__ __forceinline__ void rect_inverse(float2 (&v)[S::V], float2* lds, con
     for (int q = 0; q < S::TA; ++q) dft_slice<RA, true>(v + RA * q);
 }
 
+// c ? a : b by value (the conditional operator on array elements selects their
+// addresses, which would put the arrays in scratch memory).
+__device__ __forceinline__ float2 pick(bool c, float2 a, float2 b) { return make_float2(c ? a.x : b.x, c ? a.y : b.y); }
+
+// A Fourier step on layout D that combines every mode with its mirror:
+//   mirror_put, barrier, mirror_step, barrier, mirror_get
+// with `sz` 8 RD elements of LDS.  f.pair(k2, ky, kx, za, zb, sa, sb) takes
+// Z(k) and Z(-k) of task a's mode k = (ky, kx), ky = k1a + RC k2, and gives both
+// new values.  The modes of the tasks that mirror themselves go through sz to
+// 4 RD threads, one mode each (left to the two threads that hold them, they
+// would be 2 RD modes one after the other while every other wave waits at the
+// barrier: 2 us of a 128^2 mass-mapping sweep); f.single(ky, kx, z, zm) gives the
+// new value of one of them.
+template <typename S>
+__device__ __forceinline__ void mirror_put(const float2 (&v)[S::V], const DPair& dp, float2* sz) {
+    if (dp.self) {
+        float2* o = sz + (dp.zero ? 0 : 2 * S::RD);  // tasks (0, 0), (W/2, 0), (0, RC/2), (W/2, RC/2)
+#pragma unroll
+        for (int e = 0; e < S::V; ++e) o[e] = v[e];
+    }
+}
+template <typename S>
+__device__ __forceinline__ void mirror_get(float2 (&v)[S::V], const DPair& dp, const float2* sz) {
+    if (dp.self) {
+        const float2* o = sz + 4 * S::RD + (dp.zero ? 0 : 2 * S::RD);
+#pragma unroll
+        for (int e = 0; e < S::V; ++e) v[e] = o[e];
+    }
+}
+template <typename S, typename F>
+__device__ __forceinline__ void mirror_step(float2 (&v)[S::V], const DPair& dp, unsigned tid, float2* sz, F&& f) {
+    constexpr int RC = S::RC, RD = S::RD;
+    static_assert(S::NT >= 4 * RD, "one thread per self-mirrored mode");
+    float2 om[RD];
+#pragma unroll
+    for (int k2 = 0; k2 < RD; ++k2) {
+        __builtin_amdgcn_sched_barrier(0);
+        const float2 zb = pick(dp.zero, v[RD + (RD - k2) % RD], v[2 * RD - 1 - k2]);
+        float2 sa;
+        f.pair(k2, dp.k1a + RC * k2, dp.kxa, v[k2], zb, sa, om[k2]);
+        v[k2] = sa;
+    }
+#pragma unroll
+    for (int k2 = 0; k2 < RD; ++k2) v[RD + k2] = pick(dp.zero, om[(RD - k2) % RD], om[RD - 1 - k2]);
+    if (tid < 4 * RD) {
+        __builtin_amdgcn_sched_barrier(0);
+        const unsigned k2 = tid % RD, task = tid / RD;
+        const unsigned m = task < 2 ? (RD - k2) % RD : RD - 1 - k2;
+        sz[4 * RD + tid] = f.single((task < 2 ? 0 : RC / 2) + RC * k2, task % 2 ? S::W / 2 : 0, sz[tid],
+                                    sz[tid - k2 + m]);
+    }
+}
+
+// The square fields of the persistent sampler's mirrored forms.
+template <int N> struct SquareShape;
+template <> struct SquareShape<32> { using type = Rect<32, 32, 16, 8, 4, 4, 8>; };
+template <> struct SquareShape<64> { using type = Rect<64, 64, 16, 8, 8, 8, 8>; };
+template <> struct SquareShape<128> { using type = Rect<128, 128, 16, 8, 16, 16, 8>; };
+
 }  // namespace
 
 }  // namespace mf

@@ -16,7 +16,7 @@
 // field is transformed back.
 #include "mf_device.hpp"
 #include "mf_resident.hpp"
-#include "mf_resident_fft.hpp"
+#include "mf_rect_fft.hpp"
 #include "mf_shear.hpp"
 
 namespace mf {
@@ -36,15 +36,6 @@ __device__ __forceinline__ float2 ks(unsigned ky, unsigned kx) {
     return make_float2((x * x - y * y) * r, 2.f * x * y * r);
 }
 
-// D at the mirror -k of (ky, kx): equal to D(k), except that on exactly one
-// Nyquist line (where -k aliases to the same frequency in that component) the
-// mixed term changes sign.
-template <int N>
-__device__ __forceinline__ float2 ks_mirror(float2 d, unsigned ky, unsigned kx) {
-    const bool flip = (ky == (unsigned)(N / 2)) != (kx == (unsigned)(N / 2));
-    return make_float2(d.x, flip ? -d.y : d.y);
-}
-
 template <int N>
 __device__ __forceinline__ unsigned mirror_index(unsigned ky, unsigned kx) {
     return ((N - ky) & (N - 1)) * N + ((N - kx) & (N - 1));
@@ -58,90 +49,119 @@ struct Filt {
     float fp, fm, wp, wm;
 };
 
-// f/n and w/n of the E and B fields at one mode (the 1/n of the inverse
-// transform folded in), combined as (f_+, f_-, w_+, w_-).  At k = 0 the
-// messenger variance is taken to infinity, which leaves f = 0 and the prior w.
-__device__ __forceinline__ Filt filt(float nP, float r, float T, float inv_n, float n, bool k0) {
-    const float Te = k0 ? 1e20f : T;
-    const float nPB = r * nP;
-    const float rE = __builtin_amdgcn_rcpf(nP + Te), rB = __builtin_amdgcn_rcpf(nPB + Te);
-    const float fE = k0 ? 0.f : nP * rE * inv_n;
-    const float fB = k0 ? 0.f : nPB * rB * inv_n;
-    const float wE = __builtin_amdgcn_sqrtf(n * nP * (Te * rE)) * inv_n;
-    const float wB = __builtin_amdgcn_sqrtf(n * nPB * (Te * rB)) * inv_n;
-    return {0.5f * (fE + fB), 0.5f * (fE - fB), 0.5f * (wE + wB), 0.5f * (wE - wB)};
+// (f_+, f_-, w_+, w_-) of one mode off k = 0, the 1/n of the inverse transform
+// and the normals' sqrt(2 ln 2) folded in: with h = f / 2n, w / 2n = sqrt(h T / 2).
+__device__ __forceinline__ Filt filt(float nP, float r, float T, float n) {
+    const float c = 0.5f / n, g = 0.5f * kBoxMuller2 * T;
+    const float hE = nP * c * __builtin_amdgcn_rcpf(nP + T);
+    const float hB = nP * (r * c) * __builtin_amdgcn_rcpf(fmaf(r, nP, T));
+    const float wE = __builtin_amdgcn_sqrtf(hE * g), wB = __builtin_amdgcn_sqrtf(hB * g);
+    return {hE + hB, hE - hB, wE + wB, wE - wB};
 }
+// The Fourier step kappa^(k) = f_+ u(k) + f_- conj(u(-k)) + w_+ eta(k) + w_- conj(eta(-k)),
+// u = conj(D) Z, times D unless the sweep emits kappa.  eta: the mode variates
+// in LDS.  D(-k) equals D(k), except that on exactly one Nyquist line (where -k
+// aliases to the same frequency in that component) the mixed term changes sign.
+template <int N, bool NOISE, bool TIMES_D>
+struct ShearStep {
+    using S = typename SquareShape<N>::type;
+    const float* nP;
+    const float2* eta;
+    float r, T;
+    float x, x2, y1;  // k_1 of task a, its square, and its ky mod RC
+    bool nyq_x;       // task a lies on the Nyquist column
+    __device__ __forceinline__ ShearStep(const float* nP_, const float2* eta_, float r_, float T_, const DPair& dp)
+        : nP(nP_), eta(eta_), r(r_), T(T_), x((float)signed_freq<N>(dp.kxa)), x2(x * x), y1((float)dp.k1a),
+          nyq_x(dp.kxa == (unsigned)(N / 2)) {}
+    // kappa^ of a mode from u, u of its mirror, and both variates
+    __device__ __forceinline__ float2 mode(const Filt& c, float2 u, float2 um, float2 e, float2 em, float2 d) const {
+        float2 k = make_float2(fmaf(c.fp, u.x, c.fm * um.x), fmaf(c.fp, u.y, -c.fm * um.y));
+        if constexpr (NOISE) {
+            k = make_float2(fmaf(c.wp, e.x, k.x), fmaf(c.wp, e.y, k.y));
+            k = make_float2(fmaf(c.wm, em.x, k.x), fmaf(-c.wm, em.y, k.y));
+        }
+        return TIMES_D ? cmul(k, d) : k;
+    }
+    __device__ __forceinline__ void pair(int k2, unsigned ky, unsigned kx, float2 za, float2 zb, float2& sa,
+                                         float2& sb) const {
+        const Filt c = filt(nP[ky * N + kx], r, T, (float)(N * N));
+        // ky = k1 + RC k2 is below the Nyquist row exactly for k2 < RD/2
+        const float y = y1 + (float)(S::RC * k2 - (k2 >= S::RD / 2 ? N : 0));
+        const float q = __builtin_amdgcn_rcpf(fmaf(y, y, x2));  // k = 0 mirrors itself: never here
+        const float2 d = make_float2(fmaf(-y, y, x2) * q, 2.f * x * y * q);
+        const bool flip = k2 == S::RD / 2 ? (y1 == 0.f) != nyq_x : nyq_x;
+        const float2 dm = make_float2(d.x, flip ? -d.y : d.y);
+        const float2 u = mulc(za, d), um = mulc(zb, dm);
+        float2 e = make_float2(0.f, 0.f), em = e;
+        if constexpr (NOISE) {
+            e = eta[ky * N + kx];
+            em = eta[mirror_index<N>(ky, kx)];
+        }
+        sa = mode(c, u, um, e, em, d);
+        sb = mode(c, um, u, em, e, dm);
+    }
+    __device__ __forceinline__ float2 single(unsigned ky, unsigned kx, float2 z, float2 zm) const {
+        const bool k0 = ky == 0 && kx == 0;
+        // at k = 0 (no data) f = 0, and the messenger variance taken to infinity leaves the prior w
+        Filt c = filt(nP[ky * N + kx], r, k0 ? 1e20f : T, (float)(N * N));
+        c.fp = k0 ? 0.f : c.fp;
+        c.fm = k0 ? 0.f : c.fm;
+        const float2 d = ks<N>(ky, kx);
+        const bool flip = (ky == (unsigned)(N / 2)) != (kx == (unsigned)(N / 2));
+        float2 e = make_float2(0.f, 0.f), em = e;
+        if constexpr (NOISE) {
+            e = eta[ky * N + kx];
+            em = eta[mirror_index<N>(ky, kx)];
+        }
+        return mode(c, mulc(z, d), mulc(zm, make_float2(d.x, flip ? -d.y : d.y)), e, em, d);
+    }
+};
 
+// Every thread must call it.  One mode's coefficients (two reciprocals, two
+// square roots) and D serve the mode and its mirror; the draws go through LDS,
+// since a Philox call's two modes sit in neighbouring lanes.  VALU-bound: about
+// 3,400 instructions per wave and sweep at 128^2 (4,900 with Z and eta exchanged
+// for the mirror and the coefficients evaluated three times), 88% of the issue
+// rate; 512 chains x 80 sweeps 5.23 -> 4.12 ms.
 template <int N>
-__device__ __forceinline__ void harmonic_shear(float2 (&v)[16], float2* lds, const ShearArgs& a, const ProbDev& pr,
-                                               float T, uint32_t sweep, int chain, unsigned tid) {
-    constexpr int P = Res<N>::P;
-    __syncthreads();  // other threads may still read the forward transform's last exchange
-    constexpr float n = (float)(N * N);
-    constexpr float inv_n = 1.0f / (float)(N * N);
-    const unsigned jx = tid % (N / 2), k1 = tid / (N / 2);
+__device__ __forceinline__ void harmonic_shear(float2 (&v)[16], float2* lds, float2* sz, const ShearArgs& a, const ProbDev& pr,
+                                               float T, uint32_t sweep, int chain, unsigned tid, bool times_d) {
+    using S = typename SquareShape<N>::type;
+    const DPair dp = d_pair<S>(tid);
+    mirror_put<S>(v, dp, sz);
     const float* nP = a.nP + pr.pix_off;
+    if (a.stochastic) {
+        __syncthreads();  // other threads may still read the forward transform's last exchange
+        const unsigned jx = tid % (N / 2), k1 = tid / (N / 2);
 #pragma unroll
-    for (int k2 = 0; k2 < 8; ++k2) {
-        const unsigned ky = k1 + P * k2;
-        *reinterpret_cast<float4*>(lds + ky * N + 2 * jx) = make_float4(v[k2].x, v[k2].y, v[8 + k2].x, v[8 + k2].y);
-    }
-    __syncthreads();
-    // filter part: f_+ u(k) + f_- conj(u(-k)), u = conj(D) Z
-#pragma unroll
-    for (int k2 = 0; k2 < 8; ++k2) {
-        __builtin_amdgcn_sched_barrier(0);
-        const unsigned ky = k1 + P * k2;
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const unsigned kx = 2 * jx + q;
-            const unsigned mi = mirror_index<N>(ky, kx);
-            const Filt c = filt(nP[ky * N + kx], a.b_ratio, T, inv_n, n, ky == 0 && kx == 0);
-            const float2 d = ks<N>(ky, kx);
-            const float2 u = mulc(v[8 * q + k2], d);
-            const float2 um = mulc(lds[mi], ks_mirror<N>(d, ky, kx));
-            v[8 * q + k2] = make_float2(fmaf(c.fp, u.x, c.fm * um.x), fmaf(c.fp, u.y, -c.fm * um.y));
+        for (int k2 = 0; k2 < 8; ++k2) {
+            __builtin_amdgcn_sched_barrier(0);
+            const unsigned ky = k1 + S::RC * k2;
+            const uint32_t e2 = (uint32_t)(ky * (N / 2) + jx);
+            const Polar2 z = pair_polar(e2, sweep, (uint32_t)pr.pid, kStageHarmonic, (uint32_t)chain, a.key0, a.key1);
+            st2(lds, ky * N + 2 * jx, make_float2(z.a.r * z.a.c, z.a.r * z.a.s), make_float2(z.b.r * z.b.c, z.b.r * z.b.s));
         }
+        __syncthreads();
+        if (times_d) mirror_step<S>(v, dp, tid, sz, ShearStep<N, true, true>(nP, lds, a.b_ratio, T, dp));
+        else mirror_step<S>(v, dp, tid, sz, ShearStep<N, true, false>(nP, lds, a.b_ratio, T, dp));
+    } else {
+        __syncthreads();
+        if (times_d) mirror_step<S>(v, dp, tid, sz, ShearStep<N, false, true>(nP, nullptr, a.b_ratio, T, dp));
+        else mirror_step<S>(v, dp, tid, sz, ShearStep<N, false, false>(nP, nullptr, a.b_ratio, T, dp));
     }
     __syncthreads();
-    if (!a.stochastic) return;
-    // noise: w_+ eta(k) now, eta to LDS for w_- conj(eta(-k))
-#pragma unroll
-    for (int k2 = 0; k2 < 8; ++k2) {
-        __builtin_amdgcn_sched_barrier(0);
-        const unsigned ky = k1 + P * k2;
-        const uint32_t e2 = (uint32_t)(ky * (N / 2) + jx);
-        const Normals2 z = pair_normals(e2, sweep, (uint32_t)pr.pid, kStageHarmonic, (uint32_t)chain, a.key0, a.key1);
-        *reinterpret_cast<float4*>(lds + ky * N + 2 * jx) = make_float4(z.a.x, z.a.y, z.b.x, z.b.y);
-        const Filt c0 = filt(nP[ky * N + 2 * jx], a.b_ratio, T, inv_n, n, ky == 0 && jx == 0);
-        const Filt c1 = filt(nP[ky * N + 2 * jx + 1], a.b_ratio, T, inv_n, n, false);
-        v[k2] = make_float2(fmaf(c0.wp, z.a.x, v[k2].x), fmaf(c0.wp, z.a.y, v[k2].y));
-        v[8 + k2] = make_float2(fmaf(c1.wp, z.b.x, v[8 + k2].x), fmaf(c1.wp, z.b.y, v[8 + k2].y));
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k2 = 0; k2 < 8; ++k2) {
-        __builtin_amdgcn_sched_barrier(0);
-        const unsigned ky = k1 + P * k2;
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const unsigned kx = 2 * jx + q;
-            const Filt c = filt(nP[ky * N + kx], a.b_ratio, T, inv_n, n, ky == 0 && kx == 0);
-            const float2 em = lds[mirror_index<N>(ky, kx)];
-            float2& z = v[8 * q + k2];
-            z = make_float2(fmaf(c.wm, em.x, z.x), fmaf(-c.wm, em.y, z.y));
-        }
-    }
-    __syncthreads();
+    mirror_get<S>(v, dp, sz);
 }
 
 template <int N>
-__global__ __launch_bounds__(Res<N>::NT, 4) void resident_shear_kernel(ShearArgs a) {
-    constexpr int P = Res<N>::P;
-    __shared__ __align__(16) float2 lds[Res<N>::LDS];
-    __shared__ float2 twl[Res<N>::TWS];  // twiddle tables of the four passes
+__global__ __launch_bounds__(SquareShape<N>::type::NT, 4) void resident_shear_kernel(ShearArgs a) {
+    using S = typename SquareShape<N>::type;
+    constexpr int P = S::RB;
+    __shared__ __align__(16) float2 lds[S::LDS];
+    __shared__ float2 twl[S::TWS];  // twiddle tables of the four passes
+    __shared__ float2 sz[8 * S::RD];
     const unsigned tid = threadIdx.x;
-    fill_twiddle_tables<N>(twl, a.tw, tid);
+    rect_twiddles<S>(twl, a.tw, a.tw, 1, tid);
     __syncthreads();
     const ItemDev it = a.items[blockIdx.x];
     const ProbDev pr = a.probs[it.prob];
@@ -182,27 +202,28 @@ __global__ __launch_bounds__(Res<N>::NT, 4) void resident_shear_kernel(ShearArgs
                     s0 = make_float2(fmaf(1.f - a0, s0.x, g0.x), fmaf(1.f - a0, s0.y, g0.y));
                     s1 = make_float2(fmaf(1.f - a1, s1.x, g1.x), fmaf(1.f - a1, s1.y, g1.y));
                     if (a.stochastic) {
-                        const Normals2 z = pair_normals(e2, sweep, (uint32_t)pr.pid, kStagePixel, (uint32_t)it.pair,
-                                                        a.key0, a.key1);
-                        const float sg0 = __builtin_amdgcn_sqrtf(fmaxf(T * (1.f - a0), 0.f));
-                        const float sg1 = __builtin_amdgcn_sqrtf(fmaxf(T * (1.f - a1), 0.f));
-                        s0 = make_float2(fmaf(sg0, z.a.x, s0.x), fmaf(sg0, z.a.y, s0.y));
-                        s1 = make_float2(fmaf(sg1, z.b.x, s1.x), fmaf(sg1, z.b.y, s1.y));
+                        const Polar2 z = pair_polar(e2, sweep, (uint32_t)pr.pid, kStagePixel, (uint32_t)it.pair,
+                                                    a.key0, a.key1);
+                        const float r0 = z.a.r * __builtin_amdgcn_sqrtf(fmaxf(kBoxMuller2 * T * (1.f - a0), 0.f));
+                        const float r1 = z.b.r * __builtin_amdgcn_sqrtf(fmaxf(kBoxMuller2 * T * (1.f - a1), 0.f));
+                        s0 = make_float2(fmaf(r0, z.a.c, s0.x), fmaf(r0, z.a.s, s0.y));
+                        s1 = make_float2(fmaf(r1, z.b.c, s1.x), fmaf(r1, z.b.s, s1.y));
                     }
                 }
             }
-            forward_fft<N>(v, lds, tw, t);
+            rect_forward<S>(v, lds, tw, t, d_pair<S>(t));
             unsigned t2 = tid;
             asm volatile("" : "+v"(t2));
-            harmonic_shear<N>(v, lds, a, pr, T, sweep, it.pair, t2);
             const bool last = lv == a.lv.n - 1 && s == a.lv.sweeps[lv] - 1;
             const bool emit = a.samples && k >= a.burn_in && ((k - a.burn_in + 1) % a.thin) == 0;
-            if (emit || (last && a.kappa_out)) {
+            const bool write = emit || (last && a.kappa_out);
+            harmonic_shear<N>(v, lds, sz, a, pr, T, sweep, it.pair, t2, !write);
+            if (write) {
                 // kappa = F^-1 kappa^, written out, then transformed back
                 unsigned t3 = tid;
                 asm volatile("" : "+v"(t3));
                 const float2* tw3 = twl + per_sweep_zero();
-                inverse_fft<N>(v, lds, tw3, t3);
+                rect_inverse<S>(v, lds, tw3, t3, d_pair<S>(t3));
                 float2* o;
                 if (emit) {
                     const int64_t slot = (k - a.burn_in + 1) / a.thin - 1;
@@ -219,25 +240,21 @@ __global__ __launch_bounds__(Res<N>::NT, 4) void resident_shear_kernel(ShearArgs
                 }
                 unsigned t4 = tid;
                 asm volatile("" : "+v"(t4));
-                forward_fft<N>(v, lds, tw3, t4);
+                const DPair dp = d_pair<S>(t4);
+                rect_forward<S>(v, lds, tw3, t4, dp);
+                // the unnormalised forward transform returned n kappa^
+                constexpr float back = 1.0f / (float)(N * N);
+#pragma unroll
+                for (int e = 0; e < 16; ++e) {
+                    const unsigned ky = (e < 8 ? dp.k1a : dp.k1b) + S::RC * (e % 8), kx = e < 8 ? dp.kxa : dp.kxb;
+                    v[e] = cmul(v[e], cscale(ks<N>(ky, kx), back));
+                }
             }
-            // next state: F^-1 (D kappa^); after the round trip through pixel space
-            // the unnormalised forward transform returned n kappa^
-            const float back = (emit || (last && a.kappa_out)) ? 1.0f / (float)(N * N) : 1.0f;
+            // next state: F^-1 (D kappa^)
             unsigned t5 = tid;
             asm volatile("" : "+v"(t5));
             const float2* tw5 = twl + per_sweep_zero();
-            {
-                const unsigned jx = t5 % (N / 2), k1 = t5 / (N / 2);
-#pragma unroll
-                for (int k2 = 0; k2 < 8; ++k2) {
-                    const unsigned ky = k1 + P * k2;
-#pragma unroll
-                    for (int q = 0; q < 2; ++q)
-                        v[8 * q + k2] = cmul(v[8 * q + k2], cscale(ks<N>(ky, 2 * jx + q), back));
-                }
-            }
-            inverse_fft<N>(v, lds, tw5, t5);
+            rect_inverse<S>(v, lds, tw5, t5, d_pair<S>(t5));
         }
     }
     if (a.state_out) {
@@ -255,9 +272,9 @@ __global__ __launch_bounds__(Res<N>::NT, 4) void resident_shear_kernel(ShearArgs
 hipError_t launch_resident_shear(int N, const ShearArgs& a, hipStream_t s) {
     const dim3 grid((unsigned)a.n_items);
     switch (N) {
-        case 32: hipLaunchKernelGGL(resident_shear_kernel<32>, grid, dim3(Res<32>::NT), 0, s, a); break;
-        case 64: hipLaunchKernelGGL(resident_shear_kernel<64>, grid, dim3(Res<64>::NT), 0, s, a); break;
-        case 128: hipLaunchKernelGGL(resident_shear_kernel<128>, grid, dim3(Res<128>::NT), 0, s, a); break;
+        case 32: hipLaunchKernelGGL(resident_shear_kernel<32>, grid, dim3(SquareShape<32>::type::NT), 0, s, a); break;
+        case 64: hipLaunchKernelGGL(resident_shear_kernel<64>, grid, dim3(SquareShape<64>::type::NT), 0, s, a); break;
+        case 128: hipLaunchKernelGGL(resident_shear_kernel<128>, grid, dim3(SquareShape<128>::type::NT), 0, s, a); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

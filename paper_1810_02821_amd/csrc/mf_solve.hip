@@ -145,11 +145,10 @@ __global__ __launch_bounds__(SolveShape<N>::type::NT, N == 128 ? 2 : 4) void res
         float2 z[V];
 #pragma unroll
         for (int k2 = 0; k2 < RD; ++k2) {
-            const float2 a0 = v[(RD - k2) % RD], a1 = v[RD - 1 - k2];
-            const float2 b0 = v[RD + (RD - k2) % RD], b1 = v[2 * RD - 1 - k2];
-            const float2 ma = dp.zero ? a0 : a1, mb = dp.zero ? b0 : b1;
-            z[k2] = dp.self ? ma : mb;
-            z[RD + k2] = dp.self ? mb : ma;
+            const float2 ma = pick(dp.zero, v[(RD - k2) % RD], v[RD - 1 - k2]);
+            const float2 mb = pick(dp.zero, v[RD + (RD - k2) % RD], v[2 * RD - 1 - k2]);
+            z[k2] = pick(dp.self, ma, mb);
+            z[RD + k2] = pick(dp.self, mb, ma);
         }
 #pragma unroll
         for (int e = 0; e < V; ++e)
