@@ -9,7 +9,8 @@
 //     S(k) = f_+ Z(k) + f_- conj(Z(-k)) + w_+ eta(k) + w_- conj(eta(-k))
 // gives chain A (real part of the inverse transform) the update f_A Z_A + w_A
 // noise and chain B (imaginary part) f_B Z_B + w_B noise, exactly.  The
-// mirrored values Z(-k) and eta(-k) come through LDS.
+// transform leaves k and -k in one thread (mf_rect_fft.hpp); eta goes through
+// LDS, since a Philox call's two modes sit in neighbouring lanes.
 //
 // The amplitudes given the signal are inverse-gamma: theta_b = (2 beta_0 +
 // sigma_b / n^2) / x_b, with sigma_b the band power of the chain's signal and
@@ -18,7 +19,7 @@
 // freedom, counter word 1 = the global iteration).
 #include "mf_device.hpp"
 #include "mf_resident.hpp"
-#include "mf_resident_fft.hpp"
+#include "mf_rect_fft.hpp"
 #include "mf_spectrum.hpp"
 
 namespace mf {
@@ -31,8 +32,7 @@ constexpr int kNB = kMaxBandsPerProblem;
 struct SpecShared {
     float4 coef[kNB];      // (f_A/n, w_A/n, f_B/n, w_B/n) per band
     double theta[2][kNB];  // current amplitudes, chains A and B
-    double pw[2][kNB];     // band powers of the last signal, in units of n^2
-    double chi[2][kNB];    // chi-square sums
+    double sum[2][2][kNB]; // [0]: band powers of the last signal, in units of n^2; [1]: chi-square sums
     int32_t dof[kNB];      // degrees of freedom per band
     int32_t pre[kNB + 1];  // their prefix sums (flat index of each band's first variate)
 };
@@ -42,143 +42,155 @@ __device__ __forceinline__ unsigned mirror(unsigned ky, unsigned kx) {
     return ((N - ky) & (N - 1)) * N + ((N - kx) & (N - 1));
 }
 
-// f/n and w/n of both chains for every band, from the current amplitudes.
-__device__ __forceinline__ void refresh_coef(SpecShared& sh, int nb, double T, double n) {
-    for (int b = threadIdx.x; b < nb; b += blockDim.x) {
-        float c[4];
+// f/n and w/n of both chains for band b, from the current amplitudes.
+__device__ __forceinline__ void refresh_coef(SpecShared& sh, int b, double T, double n) {
+    float c[4];
 #pragma unroll
-        for (int ch = 0; ch < 2; ++ch) {
-            const double nP = n * sh.theta[ch][b];
-            const double f = nP / (nP + T);
-            const double w = sqrt(n * nP * T / (nP + T));
-            c[2 * ch] = (float)(f / n);
-            c[2 * ch + 1] = (float)(w / n);
-        }
-        sh.coef[b] = make_float4(c[0], c[1], c[2], c[3]);
+    for (int ch = 0; ch < 2; ++ch) {
+        const double nP = n * sh.theta[ch][b];
+        const double f = nP / (nP + T);
+        const double w = sqrt(n * nP * T / (nP + T));
+        c[2 * ch] = (float)(f / n);
+        c[2 * ch + 1] = (float)(w / n);
     }
+    sh.coef[b] = make_float4(c[0], c[1], c[2], c[3]);
 }
 
-// Fourier-space step on layout D (thread (k1, jx) holds modes (k1 + P k2, 2 jx + q)
-// at v[8 q + k2]); on return v holds S(k)/n.  Every thread must call it.
+// The Fourier step S(k)/n of a mode and its mirror (one band, one set of coefficients).
 template <int N>
-__device__ __forceinline__ void harmonic_pair(float2 (&v)[16], float2* lds, const SpectrumArgs& a,
+struct SpecStep {
+    const float4* coef;
+    const int16_t* band;
+    const float2* eta;
+    __device__ __forceinline__ float2 mode(float fp, float fm, float wp, float wm, float2 z, float2 zm, float2 e,
+                                           float2 em) const {
+        float2 s = make_float2(fmaf(fp, z.x, fm * zm.x), fmaf(fp, z.y, -fm * zm.y));
+        s = make_float2(fmaf(wp, e.x, s.x), fmaf(wp, e.y, s.y));
+        return make_float2(fmaf(wm, em.x, s.x), fmaf(-wm, em.y, s.y));
+    }
+    __device__ __forceinline__ void pair(int, unsigned ky, unsigned kx, float2 za, float2 zb, float2& sa,
+                                         float2& sb) const {
+        const float4 c = coef[band[ky * N + kx]];
+        const float fp = 0.5f * (c.x + c.z), fm = 0.5f * (c.x - c.z);
+        const float wp = 0.5f * (c.y + c.w), wm = 0.5f * (c.y - c.w);
+        const float2 e = eta[ky * N + kx], em = eta[mirror<N>(ky, kx)];
+        sa = mode(fp, fm, wp, wm, za, zb, e, em);
+        sb = mode(fp, fm, wp, wm, zb, za, em, e);
+    }
+    __device__ __forceinline__ float2 single(unsigned ky, unsigned kx, float2 z, float2 zm) const {
+        float2 sa, sb;
+        pair(0, ky, kx, z, zm, sa, sb);
+        return sa;
+    }
+};
+
+// Fourier-space step on layout D; on return v holds S(k)/n.  Every thread must call it.
+template <int N>
+__device__ __forceinline__ void harmonic_pair(float2 (&v)[16], float2* lds, float2* sz, const SpectrumArgs& a,
                                               const ProbDev& pr, const SpecShared& sh, uint32_t sweep,
                                               int pair, unsigned tid) {
-    constexpr int P = Res<N>::P;
-    const unsigned jx = tid % (N / 2), k1 = tid / (N / 2);
-    const int16_t* band = a.band + pr.pix_off;
+    using S = typename SquareShape<N>::type;
+    const DPair dp = d_pair<S>(tid);
+    mirror_put<S>(v, dp, sz);
     __syncthreads();  // other threads may still read the forward transform's last exchange
-    // 1. Z to LDS in natural mode order
-#pragma unroll
-    for (int k2 = 0; k2 < 8; ++k2) {
-        const unsigned ky = k1 + P * k2;
-        *reinterpret_cast<float4*>(lds + ky * N + 2 * jx) = make_float4(v[k2].x, v[k2].y, v[8 + k2].x, v[8 + k2].y);
-    }
-    __syncthreads();
-    // 2. filter part: f_+ Z(k) + f_- conj(Z(-k))
-#pragma unroll
-    for (int k2 = 0; k2 < 8; ++k2) {
-        const unsigned ky = k1 + P * k2;
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const unsigned kx = 2 * jx + q;
-            const float4 c = sh.coef[band[ky * N + kx]];
-            const float fp = 0.5f * (c.x + c.z), fm = 0.5f * (c.x - c.z);
-            const float2 zm = lds[mirror<N>(ky, kx)];
-            float2& z = v[8 * q + k2];
-            z = make_float2(fmaf(fp, z.x, fm * zm.x), fmaf(fp, z.y, -fm * zm.y));
-        }
-    }
-    __syncthreads();
-    // 3. noise part: w_+ eta(k), and eta to LDS for the mirrored term
+    const unsigned jx = tid % (N / 2), k1 = tid / (N / 2);
 #pragma unroll
     for (int k2 = 0; k2 < 8; ++k2) {
         __builtin_amdgcn_sched_barrier(0);
-        const unsigned ky = k1 + P * k2;
+        const unsigned ky = k1 + S::RC * k2;
         const uint32_t e2 = (uint32_t)(ky * (N / 2) + jx);
         const Normals2 z = pair_normals(e2, sweep, (uint32_t)pr.pid, kStageHarmonic, (uint32_t)pair, a.key0, a.key1);
-        *reinterpret_cast<float4*>(lds + ky * N + 2 * jx) = make_float4(z.a.x, z.a.y, z.b.x, z.b.y);
-        const float4 c0 = sh.coef[band[ky * N + 2 * jx]];
-        const float4 c1 = sh.coef[band[ky * N + 2 * jx + 1]];
-        const float wp0 = 0.5f * (c0.y + c0.w), wp1 = 0.5f * (c1.y + c1.w);
-        v[k2] = make_float2(fmaf(wp0, z.a.x, v[k2].x), fmaf(wp0, z.a.y, v[k2].y));
-        v[8 + k2] = make_float2(fmaf(wp1, z.b.x, v[8 + k2].x), fmaf(wp1, z.b.y, v[8 + k2].y));
+        st2(lds, ky * N + 2 * jx, z.a, z.b);
     }
     __syncthreads();
-    // 4. w_- conj(eta(-k))
-#pragma unroll
-    for (int k2 = 0; k2 < 8; ++k2) {
-        const unsigned ky = k1 + P * k2;
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const unsigned kx = 2 * jx + q;
-            const float4 c = sh.coef[band[ky * N + kx]];
-            const float wm = 0.5f * (c.y - c.w);
-            const float2 em = lds[mirror<N>(ky, kx)];
-            float2& z = v[8 * q + k2];
-            z = make_float2(fmaf(wm, em.x, z.x), fmaf(-wm, em.y, z.y));
-        }
-    }
+    mirror_step<S>(v, dp, tid, sz, SpecStep<N>{sh.coef, a.band + pr.pix_off, lds});
     __syncthreads();
+    mirror_get<S>(v, dp, sz);
 }
 
-// Band powers of both chains of the signal S/n held on layout D:
-// X_A = (S(k) + conj S(-k))/2, X_B = (S(k) - conj S(-k))/(2i).
+// FP64 sums by band in LDS.  Each sum is kept in R copies, one for every R-th
+// lane: the modes of a wave (and the variates of a thread's run) mostly share a
+// band, and the atomics of lanes that meet in one address run one after the
+// other.  The copies take the exchange buffer, which is free between the
+// Fourier step and the inverse transform.
 template <int N>
-__device__ __forceinline__ void band_powers(const float2 (&v)[16], float2* lds, const SpectrumArgs& a,
-                                            const ProbDev& pr, SpecShared& sh, unsigned tid) {
-    constexpr int P = Res<N>::P;
-    const unsigned jx = tid % (N / 2), k1 = tid / (N / 2);
+struct BandSums {
+    using S = typename SquareShape<N>::type;
+    static constexpr int R = N == 128 ? 32 : N == 64 ? 16 : 4;
+    static_assert(4 * kNB * R * 8 <= S::LDS * 8, "the copies fit in the exchange buffer");
+    double* acc;  // [kind][chain][band][copy]
+    int nb;
+    unsigned copy;
+    __device__ __forceinline__ BandSums(float2* lds, int nb_, unsigned tid)
+        : acc(reinterpret_cast<double*>(lds)), nb(nb_), copy(tid % R) {}
+    __device__ __forceinline__ void clear(unsigned tid) const {
+        for (int i = (int)tid; i < 4 * nb * R; i += S::NT) acc[i] = 0.0;
+    }
+    __device__ __forceinline__ void add(int kind, int b, double pa, double pb) const {
+        atomicAdd(&acc[((kind * 2 + 0) * nb + b) * R + copy], pa);
+        atomicAdd(&acc[((kind * 2 + 1) * nb + b) * R + copy], pb);
+    }
+    __device__ __forceinline__ void collect(SpecShared& sh, unsigned tid) const {
+        constexpr int G = R < 8 ? R : 8;  // lanes per sum
+        for (int o = (int)tid / G; o < 4 * nb; o += S::NT / G) {
+            double x = 0.0;
+#pragma unroll
+            for (int i = 0; i < R / G; ++i) x += acc[o * R + tid % G + i * G];
+#pragma unroll
+            for (int i = G / 2; i > 0; i >>= 1) x += __shfl_xor(x, i);
+            if (tid % G == 0) sh.sum[o / (2 * nb)][(o / nb) % 2][o % nb] = x;
+        }
+    }
+};
+
+// Band powers of both chains of the signal S/n held on layout D (sz: the modes
+// that mirror themselves): X_A = (S(k) + conj S(-k))/2, X_B = (S(k) - conj
+// S(-k))/(2i).  A mode and its mirror have the same powers.
+__device__ __forceinline__ void mode_powers(float2 s, float2 m, double& pa, double& pb) {
+    const double ar = 0.5 * ((double)s.x + m.x), ai = 0.5 * ((double)s.y - m.y);
+    const double br = 0.5 * ((double)s.y + m.y), bi = 0.5 * ((double)s.x - m.x);
+    pa = ar * ar + ai * ai;
+    pb = br * br + bi * bi;
+}
+template <int N>
+__device__ __forceinline__ void band_powers(const float2 (&v)[16], const float2* sz, const SpectrumArgs& a,
+                                            const ProbDev& pr, const BandSums<N>& bs, unsigned tid) {
+    using S = typename SquareShape<N>::type;
+    constexpr int RC = S::RC, RD = S::RD;
+    const DPair dp = d_pair<S>(tid);
     const int16_t* band = a.band + pr.pix_off;
+    double pa, pb;
+    if (!dp.self) {
 #pragma unroll
-    for (int k2 = 0; k2 < 8; ++k2) {
-        const unsigned ky = k1 + P * k2;
-        *reinterpret_cast<float4*>(lds + ky * N + 2 * jx) = make_float4(v[k2].x, v[k2].y, v[8 + k2].x, v[8 + k2].y);
-    }
-    __syncthreads();
-#pragma unroll
-    for (int k2 = 0; k2 < 8; ++k2) {
-        const unsigned ky = k1 + P * k2;
-        int b[2];
-        double pa[2], pb[2];
-#pragma unroll
-        for (int q = 0; q < 2; ++q) {
-            const unsigned kx = 2 * jx + q;
-            b[q] = band[ky * N + kx];
-            const float2 s = v[8 * q + k2];
-            const float2 m = lds[mirror<N>(ky, kx)];
-            const double ar = 0.5 * ((double)s.x + m.x), ai = 0.5 * ((double)s.y - m.y);
-            const double br = 0.5 * ((double)s.y + m.y), bi = 0.5 * ((double)s.x - m.x);
-            pa[q] = ar * ar + ai * ai;
-            pb[q] = br * br + bi * bi;
-        }
-        // the two modes of a thread are neighbours in k_x and mostly share a band
-        if (b[0] == b[1]) {
-            atomicAdd(&sh.pw[0][b[0]], pa[0] + pa[1]);
-            atomicAdd(&sh.pw[1][b[0]], pb[0] + pb[1]);
-        } else {
-#pragma unroll
-            for (int q = 0; q < 2; ++q) {
-                atomicAdd(&sh.pw[0][b[q]], pa[q]);
-                atomicAdd(&sh.pw[1][b[q]], pb[q]);
-            }
+        for (int k2 = 0; k2 < RD; ++k2) {
+            __builtin_amdgcn_sched_barrier(0);
+            mode_powers(v[k2], pick(dp.zero, v[RD + (RD - k2) % RD], v[2 * RD - 1 - k2]), pa, pb);
+            bs.add(0, band[(dp.k1a + RC * k2) * N + dp.kxa], 2.0 * pa, 2.0 * pb);
         }
     }
-    __syncthreads();
+    if (tid < 4 * RD) {
+        const unsigned k2 = tid % RD, task = tid / RD, m = task < 2 ? (RD - k2) % RD : RD - 1 - k2;
+        mode_powers(sz[4 * RD + tid], sz[4 * RD + tid - k2 + m], pa, pb);
+        bs.add(0, band[((task < 2 ? 0 : RC / 2) + RC * k2) * N + (task % 2 ? N / 2 : 0)], pa, pb);
+    }
 }
 
-// chi-square sums: thread tid owns a contiguous chunk of the flat variate index.
+// Chi-square sums: thread tid owns a contiguous run of the flat variate index,
+// which starts in band b0.
 template <int N>
-__device__ __forceinline__ void chi_square(const SpectrumArgs& a, const ProbDev& pr, SpecShared& sh, int nb,
-                                           uint32_t iteration, int pair, unsigned tid) {
-    constexpr int NT = Res<N>::NT;
+__device__ __forceinline__ int chi_run(int total) {
+    constexpr int NT = SquareShape<N>::type::NT;
+    return 2 * ((total + 2 * NT - 1) / (2 * NT));
+}
+template <int N>
+__device__ __forceinline__ void chi_square(const SpectrumArgs& a, const ProbDev& pr, const SpecShared& sh, int nb,
+                                           int b0, uint32_t iteration, int pair, const BandSums<N>& bs, unsigned tid) {
     const int total = sh.pre[nb];
-    const int chunk = 2 * ((total + 2 * NT - 1) / (2 * NT));
-    const int e0 = (int)tid * chunk;
+    const int run = chi_run<N>(total);
+    const int e0 = (int)tid * run;
     if (e0 >= total) return;
-    const int e1 = min(total, e0 + chunk);
-    int b = 0;
-    while (sh.pre[b + 1] <= e0) ++b;
+    const int e1 = min(total, e0 + run);
+    int b = b0, next = sh.pre[b0 + 1];
     double accA = 0.0, accB = 0.0;
     for (int e = e0; e < e1; e += 2) {
         const Normals2 z = pair_normals((uint32_t)(e >> 1), iteration, (uint32_t)pr.pid, kStageSpectrum,
@@ -187,29 +199,30 @@ __device__ __forceinline__ void chi_square(const SpectrumArgs& a, const ProbDev&
         for (int h = 0; h < 2; ++h) {
             const int ee = e + h;
             if (ee >= e1) break;
-            if (ee >= sh.pre[b + 1]) {
-                atomicAdd(&sh.chi[0][b], accA);
-                atomicAdd(&sh.chi[1][b], accB);
+            if (ee >= next) {
+                bs.add(1, b, accA, accB);
                 accA = accB = 0.0;
-                while (sh.pre[b + 1] <= ee) ++b;
+                do next = sh.pre[++b + 1];
+                while (next <= ee);
             }
             const float2 zz = h ? z.b : z.a;
             accA += (double)zz.x * zz.x;
             accB += (double)zz.y * zz.y;
         }
     }
-    atomicAdd(&sh.chi[0][b], accA);
-    atomicAdd(&sh.chi[1][b], accB);
+    bs.add(1, b, accA, accB);
 }
 
 template <int N>
-__global__ __launch_bounds__(Res<N>::NT, 4) void resident_spectrum_kernel(SpectrumArgs a) {
-    constexpr int P = Res<N>::P, NT = Res<N>::NT;
-    __shared__ __align__(16) float2 lds[Res<N>::LDS];
+__global__ __launch_bounds__(SquareShape<N>::type::NT, N == 128 ? 4 : N == 64 ? 3 : 2) void resident_spectrum_kernel(SpectrumArgs a) {
+    using S = typename SquareShape<N>::type;
+    constexpr int P = S::RB, NT = S::NT;
+    __shared__ __align__(16) float2 lds[S::LDS];
     __shared__ SpecShared sh;
-    __shared__ float2 twl[Res<N>::TWS];  // twiddle tables of the four passes
+    __shared__ float2 twl[S::TWS];  // twiddle tables of the four passes
+    __shared__ float2 sz[8 * S::RD];
     const unsigned tid = threadIdx.x;
-    fill_twiddle_tables<N>(twl, a.tw, tid);
+    rect_twiddles<S>(twl, a.tw, a.tw, 1, tid);
     __syncthreads();
     const ItemDev it = a.items[blockIdx.x];
     const ProbDev pr = a.probs[it.prob];
@@ -226,8 +239,6 @@ __global__ __launch_bounds__(Res<N>::NT, 4) void resident_spectrum_kernel(Spectr
         const int c = ch ? c1 : c0;
         sh.theta[ch][b] = a.theta_in ? a.theta_in[(int64_t)a.chains_pad * bbase + (int64_t)c * nb + b]
                                      : a.theta0[bbase + b];
-        sh.pw[ch][b] = 0.0;
-        sh.chi[ch][b] = 0.0;
     }
     if (tid == 0) {
         int acc = 0;
@@ -239,7 +250,9 @@ __global__ __launch_bounds__(Res<N>::NT, 4) void resident_spectrum_kernel(Spectr
         sh.pre[nb] = acc;
     }
     __syncthreads();
-    refresh_coef(sh, nb, T, n);
+    for (int b = tid; b < nb; b += NT) refresh_coef(sh, b, T, n);
+    int b0 = 0;  // band of this thread's first chi-square variate
+    for (const int e0 = (int)tid * chi_run<N>(sh.pre[nb]); b0 < nb - 1 && sh.pre[b0 + 1] <= e0;) ++b0;
 
     float2 v[16];
 #pragma unroll
@@ -289,33 +302,38 @@ __global__ __launch_bounds__(Res<N>::NT, 4) void resident_spectrum_kernel(Spectr
                     s1.y = fmaf(c.z, s1.y, fmaf(c.w, z.b.y, src.y));
                 }
             }
-            forward_fft<N>(v, lds, tw, t);
+            rect_forward<S>(v, lds, tw, t, d_pair<S>(t));
             unsigned t2 = tid;
             asm volatile("" : "+v"(t2));
-            harmonic_pair<N>(v, lds, a, pr, sh, sweep, it.pair, t2);
+            harmonic_pair<N>(v, lds, sz, a, pr, sh, sweep, it.pair, t2);
             if (k == a.sweeps - 1) {
                 // spectrum draw from this signal: band powers, chi-square sums, new amplitudes
-                band_powers<N>(v, lds, a, pr, sh, t2);
-                chi_square<N>(a, pr, sh, nb, g, it.pair, t2);
+                const BandSums<N> bs(lds, nb, tid);
+                bs.clear(tid);
+                __syncthreads();
+                band_powers<N>(v, sz, a, pr, bs, t2);
+                chi_square<N>(a, pr, sh, nb, b0, g, it.pair, bs, tid);
+                __syncthreads();
+                bs.collect(sh, tid);
                 __syncthreads();
                 const bool emit = i >= a.burn_in && ((i - a.burn_in + 1) % a.thin) == 0;
                 const int64_t slot = emit ? (i - a.burn_in + 1) / a.thin - 1 : 0;
-                for (int u = tid; u < 2 * nb; u += NT) {
-                    const int ch = u / nb, b = u % nb;
-                    const double x = sh.chi[ch][b];
-                    if (sh.dof[b] > 0 && x > 0.0) sh.theta[ch][b] = (2.0 * a.prior_beta + sh.pw[ch][b]) / x;
-                    sh.pw[ch][b] = 0.0;
-                    sh.chi[ch][b] = 0.0;
-                    const int c = ch ? c1 : c0;
-                    if (emit && a.theta_samples && c < a.chains)
-                        a.theta_samples[(int64_t)a.chains * a.n_samples * bbase +
-                                        ((int64_t)c * a.n_samples + slot) * nb + b] = sh.theta[ch][b];
+                for (int b = tid; b < nb; b += NT) {
+#pragma unroll
+                    for (int ch = 0; ch < 2; ++ch) {
+                        const double x = sh.sum[1][ch][b];
+                        if (sh.dof[b] > 0 && x > 0.0) sh.theta[ch][b] = (2.0 * a.prior_beta + sh.sum[0][ch][b]) / x;
+                        const int c = ch ? c1 : c0;
+                        if (emit && a.theta_samples && c < a.chains)
+                            a.theta_samples[(int64_t)a.chains * a.n_samples * bbase +
+                                            ((int64_t)c * a.n_samples + slot) * nb + b] = sh.theta[ch][b];
+                    }
+                    refresh_coef(sh, b, T, n);
                 }
-                __syncthreads();
-                refresh_coef(sh, nb, T, n);
-                __syncthreads();
             }
-            inverse_fft<N>(v, lds, tw, t2);
+            unsigned t3 = tid;
+            asm volatile("" : "+v"(t3));
+            rect_inverse<S>(v, lds, tw, t3, d_pair<S>(t3));
         }
         if (a.samples && i >= a.burn_in && ((i - a.burn_in + 1) % a.thin) == 0) {
             const int64_t slot = (i - a.burn_in + 1) / a.thin - 1;
@@ -350,9 +368,9 @@ __global__ __launch_bounds__(Res<N>::NT, 4) void resident_spectrum_kernel(Spectr
 hipError_t launch_resident_spectrum(int N, const SpectrumArgs& a, hipStream_t s) {
     const dim3 grid((unsigned)a.n_items);
     switch (N) {
-        case 32: hipLaunchKernelGGL(resident_spectrum_kernel<32>, grid, dim3(Res<32>::NT), 0, s, a); break;
-        case 64: hipLaunchKernelGGL(resident_spectrum_kernel<64>, grid, dim3(Res<64>::NT), 0, s, a); break;
-        case 128: hipLaunchKernelGGL(resident_spectrum_kernel<128>, grid, dim3(Res<128>::NT), 0, s, a); break;
+        case 32: hipLaunchKernelGGL(resident_spectrum_kernel<32>, grid, dim3(SquareShape<32>::type::NT), 0, s, a); break;
+        case 64: hipLaunchKernelGGL(resident_spectrum_kernel<64>, grid, dim3(SquareShape<64>::type::NT), 0, s, a); break;
+        case 128: hipLaunchKernelGGL(resident_spectrum_kernel<128>, grid, dim3(SquareShape<128>::type::NT), 0, s, a); break;
         default: return hipErrorInvalidValue;
     }
     return hipGetLastError();

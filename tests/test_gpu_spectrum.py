@@ -214,3 +214,17 @@ def test_streamed_hierarchical_graph_replays_match_eager(torch_cuda):
         assert rel(sm.cpu().numpy(), sm0.cpu().numpy()) < 1e-6
         eager.sample_spectrum(d, 5, 2, 0, 1, 1, 1)
         torch.cuda.synchronize()
+
+
+@pytest.mark.parametrize("size", [32, 64, 128])
+@pytest.mark.parametrize("bands", [2, 64])
+def test_band_sums_at_the_fewest_and_most_bands(torch_cuda, size, bands):
+    """The band sums keep several copies of each band in the exchange buffer:
+    the smallest and the largest band count (at 32^2 some of the 64 are empty)."""
+    import paper_1810_02821_amd as mf
+    prob = synth.config_bands(4, size, bands)
+    plan = mf.Plan([prob])
+    d = plan.concat([prob.d])
+    ts, smp, _, _ = plan.sample_spectrum(d, 9, 2, 1, 2, 1, 1, 1, 0.25, samples=True)
+    wt, ws = _check(plan, ts, smp, [prob], 0, 2, 2, 9, 1, 1, 1, 1, 0.25)
+    assert wt < REL_TOL and ws < REL_TOL
