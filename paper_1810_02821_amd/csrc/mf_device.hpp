@@ -273,6 +273,11 @@ __device__ __forceinline__ unsigned xcd_block(unsigned b, unsigned nb) {
     return x * q + (x < r ? x : r) + (b >> 3);
 }
 
+// Value of the neighbouring lane (lane ^ 1) in one DPP move (quad_perm 1,0,3,2).
+__device__ __forceinline__ float swap_lanes(float v) {
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, false));
+}
+
 // -------------------------------------------------------- normal variates --
 // Philox4x32 with 10 rounds (Salmon, Moraes, Dror & Shaw, SC'11): words 0 and
 // 2 are multiplied by two odd constants; the high halves are mixed with words

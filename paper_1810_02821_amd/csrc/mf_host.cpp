@@ -1396,7 +1396,7 @@ mf_status sample_impl(mf_plan p, const float* d, const mf_sample_args* g, const 
         psrc = reinterpret_cast<float2*>(pcoef + half);
         mcoef = reinterpret_cast<float4*>(psrc + half);
         MF_HIP(mf::launch_sampler_coefs(p->d_probs, (int)p->probs.size(), d, p->d_nbar, p->d_nP, pcoef, psrc, mcoef,
-                                        s));
+                                        true, s));
     }
     if (g->check_finite) MF_HIP(mf::launch_fill_int(p->d_flag, INT32_MAX, 1, s));
     for (auto& kv : p->classes) {
@@ -2207,7 +2207,7 @@ mf_status mf_sample_spectrum(mf_plan p, const float* d, const mf_spectrum_args* 
     float4* pcoef = p->coef.as<float4>();
     float2* psrc = reinterpret_cast<float2*>(pcoef + half);
     float4* mcoef = reinterpret_cast<float4*>(psrc + half);
-    MF_HIP(mf::launch_sampler_coefs(p->d_probs, (int)p->probs.size(), d, p->d_nbar, p->d_nP, pcoef, psrc, mcoef, s));
+    MF_HIP(mf::launch_sampler_coefs(p->d_probs, (int)p->probs.size(), d, p->d_nbar, p->d_nP, pcoef, psrc, mcoef, false, s));
     if (g->check_finite) MF_HIP(mf::launch_fill_int(p->d_flag, INT32_MAX, 1, s));
     for (auto& kv : p->classes) {
         const int H = kv.first.first, W = kv.first.second;

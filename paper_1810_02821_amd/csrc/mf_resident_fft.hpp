@@ -1,10 +1,9 @@
-// Register/LDS 2D FFT of the persistent kernels: one workgroup holds an
-// N x N complex field (N = 8 P, P in {4, 8, 16}), 16 values per thread
-// (N^2/16 threads).  A 2D FFT is four passes, radix-8 and radix-P along each
+// Register/LDS 2D FFT of one workgroup over an H x W complex field (H = RC RD,
+// W = RA RB), V values per thread.  A 2D FFT is four passes, two along each
 // dimension:
-//   rows    x = x0 + P m,  kx = k1 + 8 k2   (pass A: radix-8 over m,  pass B: radix-P over x0)
-//   columns y = y0 + 8 m,  ky = k1 + P k2   (pass C: radix-P over m,  pass D: radix-8 over y0)
-// with twiddles W_N^(x0 k1) after A and W_N^(y0 k1) after C.  The forward
+//   rows    x = x0 + RB m,  kx = k1 + RA k2  (pass A: radix-RA over m, pass B: radix-RB over x0)
+//   columns y = y0 + RD m,  ky = k1 + RC k2  (pass C: radix-RC over m, pass D: radix-RD over y0)
+// with twiddles W_W^(x0 k1) after A and W_H^(y0 k1) after C.  The forward
 // transform runs A, B, C, D (decimation in frequency); the inverse runs the
 // transposed passes D', C', B', A' (decimation in time), so the Fourier-space
 // update happens in pass D's registers and the pixel-space update in pass A's,
@@ -15,87 +14,34 @@
 // offsets from one base (the immediate offsets of ds_read/ds_write, no address
 // arithmetic per element), while every 16- or 32-lane phase of an LDS
 // instruction still touches distinct banks:
-//   E1  row y starts at y N + 2 s(y) + 32 (y / R1), s(y) = (P/2)(y % R1) + (y / R1) % (P/2):
-//       the R1 rows of one 16-lane phase of pass A's 16-byte accesses fall
-//       on disjoint 128-byte halves of the banks, and 16 consecutive rows
-//       (pass B's lanes) on 16 distinct 16-byte bank groups;
-//   E2  pitch N + 1 (pass B's lanes walk rows, pass C's walk columns);
-//   E3  pitch N + 1 as well (both sides' lanes walk columns).
-// Four of a sweep's twelve block barriers are not needed: in the exchanges
-// C -> C (E2 read, E3 written, and back), D -> D and A -> A each thread writes
-// exactly the addresses it has just read (E2 and E3 share a layout), and a
-// wave's LDS operations take effect in order, so no other thread can still be
-// waiting for what it overwrites.  A caller that writes LDS between two
-// transforms synchronises the block first.
-// Twiddles W_N^(a b) sit in LDS in one small table per pass, row a (the
-// thread's own index: x0 in A, k1 in B and D, y0 in C) by column b (the
-// register's), so that a thread's twiddles too lie at constant offsets from
-// one base.  Pass A's rows have pitch 9, so that the eight rows one wave reads
-// fall on distinct banks; the other passes read one or a few rows per wave.
+//   E1  row y starts at y W + 2 s(y) + 32 (y / R1), R1 = 32/RB, s(y) = (RB/2)(y % R1) + (y / R1) % (RB/2):
+//       the R1 rows of one phase of pass A's accesses fall on disjoint parts
+//       of the banks, and 16 consecutive rows (pass B's lanes) on 16 distinct
+//       16-byte bank groups;
+//   E2  pitch W + 1 (pass B's lanes walk rows, pass C's walk columns);
+//   E3  pitch W + 1 as well (both sides' lanes walk columns).
+// In the exchanges C -> C (E2 read, E3 written, and back), D -> D and A -> A
+// each thread writes exactly the addresses it has just read (E2 and E3 share a
+// layout), and a wave's LDS operations take effect in order, so no block
+// barrier is needed there: 8 a sweep.  A caller that writes the buffer between
+// two transforms synchronises the block first.
+// Twiddles W^(a b) sit in LDS in one small table per pass, row a (the thread's
+// own index: x0 in A, k1 in B and D, y0 in C) by column b (the register's), so
+// that a thread's twiddles too lie at constant offsets from one base.
+//
+// A pass-D task (kx, k1) is one radix-RD butterfly and holds the modes (k1 +
+// RC k2, kx), k2 < RD.  Two assignments of tasks to threads: DNat, neighbouring
+// columns (a Philox call's two modes in one thread or in neighbouring lanes);
+// and DPair (V = 2 RD), a task and its mirror (-kx, -k1), which holds the modes
+// -k of the first, so that a Fourier step that combines Z(k) with Z(-k) needs
+// no exchange.  Four tasks (kx in {0, W/2}, k1 in {0, RC/2}) are their own
+// mirrors; two threads take two of them each.
 #pragma once
 #include "mf_device.hpp"
 
 namespace mf {
 
 namespace {
-
-template <int N>
-struct Res {
-    static constexpr int P = N / 8;
-    static constexpr int NT = N * N / 16;                  // threads per workgroup
-    static constexpr int TB = 16 / P;                      // radix-P tasks per thread
-    static constexpr int R1 = 32 / P;                      // pass-A rows per 16-lane phase
-    static constexpr int LDS = N * N + N * P;              // float2 elements of the exchange buffer (E1's extent)
-    // twiddle tables: A [x0 < P][k1 < 8] pitch 9, B [k1 < 8][x0 < P],
-    // C [y0 < 8][k1 < P], D [k1 < P][y0 < 8]
-    static constexpr int TWA = 0, TWB = TWA + 9 * P, TWC = TWB + 8 * P, TWD = TWC + 8 * P;
-    static constexpr int TWS = TWD + 8 * P;                // float2 elements of the four tables
-};
-
-// Fill the twiddle tables from W_N^r (r < N); every product a b is below N.
-// Visible to the block after its next barrier.
-template <int N>
-__device__ __forceinline__ void fill_twiddle_tables(float2* t, const float2* __restrict__ tw, unsigned tid) {
-    constexpr int P = Res<N>::P;
-    for (unsigned e = tid; e < (unsigned)Res<N>::TWS; e += Res<N>::NT) {
-        unsigned r;
-        if (e < (unsigned)Res<N>::TWB) {
-            const unsigned q = e - Res<N>::TWA, a = q / 9, b = q % 9;
-            r = b < 8 ? a * b : 0;
-        } else if (e < (unsigned)Res<N>::TWC) {
-            const unsigned q = e - Res<N>::TWB;
-            r = (q / P) * (q % P);
-        } else if (e < (unsigned)Res<N>::TWD) {
-            const unsigned q = e - Res<N>::TWC;
-            r = (q / P) * (q % P);
-        } else {
-            const unsigned q = e - Res<N>::TWD;
-            r = (q / 8) * (q % 8);
-        }
-        t[e] = tw[r];
-    }
-}
-
-// E1 (between passes A and B): row y, column k1 P + x0
-template <int N>
-__device__ __forceinline__ unsigned e1_row(unsigned r) {
-    constexpr unsigned P = Res<N>::P, R1 = Res<N>::R1;
-    return r * N + 2 * ((P / 2) * (r % R1) + (r / R1) % (P / 2)) + 32 * (r / R1);
-}
-template <int N>
-__device__ __forceinline__ unsigned e1(unsigned r, unsigned c) {
-    return e1_row<N>(r) + c;
-}
-// E2 (between passes B and C): row y, column kx
-template <int N>
-__device__ __forceinline__ unsigned e2(unsigned r, unsigned c) {
-    return r * (N + 1) + c;
-}
-// E3 (between passes C and D): row 8 k1 + y0, column kx
-template <int N>
-__device__ __forceinline__ unsigned e3(unsigned r, unsigned c) {
-    return r * (N + 1) + c;
-}
 
 __device__ __forceinline__ void st2(float2* lds, unsigned i, float2 a, float2 b) {
     *reinterpret_cast<float4*>(lds + i) = make_float4(a.x, a.y, b.x, b.y);
@@ -141,242 +87,283 @@ __device__ __forceinline__ float2 twiddle(float2 v, const float2* __restrict__ r
     return INV ? cmulc(v, w) : cmul(v, w);
 }
 
-// ---------------------------------------------------------------- passes --
+template <int H_, int W_, int V_, int RA_, int RB_, int RC_, int RD_>
+struct Rect {
+    static constexpr int H = H_, W = W_, V = V_, RA = RA_, RB = RB_, RC = RC_, RD = RD_;
+    static_assert(H == RC * RD && W == RA * RB, "Rect shape");
+    static constexpr int NT = H * W / V;    // threads per workgroup
+    static constexpr int TA = V / RA;       // tasks per thread in passes A and D (1 or 2), B and C
+    static constexpr int TD = V / RD;
+    static constexpr int TB = V / RB;
+    static constexpr int TC = V / RC;
+    static constexpr int R1 = 32 / RB;
+    static constexpr int YC = H / V;        // step of pass C's y0 between a thread's tasks
+    static_assert(TA <= 2 && TD <= 2 && TB >= 1 && TC >= 1 && NT % W == 0, "Rect shape");
+    static constexpr int e1_base(int r) { return r * W + 2 * ((RB / 2) * (r % R1) + (r / R1) % (RB / 2)) + 32 * (r / R1); }
+    static constexpr int extent() {
+        int m = H * (W + 1);
+        for (int r = 0; r < H; ++r) m = e1_base(r) + W > m ? e1_base(r) + W : m;
+        return m;
+    }
+    static constexpr int LDS = extent();    // float2 elements of the exchange buffer
+    // twiddle tables: A [x0 < RB][k1 < RA] pitch RA + 1, B [k1 < RA][x0 < RB],
+    // C [y0 < RD][k1 < RC], D [k1 < RC][y0 < RD] pitch RD + 1
+    static constexpr int TWA = 0, TWB = TWA + (RA + 1) * RB, TWC = TWB + RA * RB, TWD = TWC + RD * RC;
+    static constexpr int TWS = TWD + (RD + 1) * RC;
+};
+
+// The tasks of a thread in pass D: task q's column kx(q) and k1(q).
+struct DPair {
+    unsigned kxa, k1a, kxb, k1b;
+    bool self;  // each task is its own mirror (else each is the other's)
+    bool zero;  // k1a = 0: mode k2 mirrors (RD - k2) mod RD, else RD - 1 - k2
+    __device__ __forceinline__ unsigned kx(int q) const { return q ? kxb : kxa; }
+    __device__ __forceinline__ unsigned k1(int q) const { return q ? k1b : k1a; }
+};
+template <typename S>
+struct DNat {
+    unsigned j, k;  // columns TD j + q, k1
+    __device__ __forceinline__ explicit DNat(unsigned tid) : j(tid % (S::W / S::TD)), k(tid / (S::W / S::TD)) {}
+    __device__ __forceinline__ unsigned kx(int q) const { return S::TD * j + q; }
+    __device__ __forceinline__ unsigned k1(int) const { return k; }
+};
+template <typename S>
+__device__ __forceinline__ DPair d_pair(unsigned tid) {
+    static_assert(S::TD == 2, "a task and its mirror per thread");
+    constexpr unsigned W = S::W, RC = S::RC;
+    const unsigned kx = tid % (W / 2), k1 = tid / (W / 2);
+    DPair p;
+    p.self = kx == 0 && (k1 == 0 || k1 == RC / 2);
+    p.zero = k1 == 0;
+    p.kxa = kx == 0 && k1 > RC / 2 ? W / 2 : kx;
+    p.k1a = k1;
+    p.kxb = p.self ? W / 2 : (W - p.kxa) % W;
+    p.k1b = p.self ? k1 : (RC - k1) % RC;
+    return p;
+}
+
+// Fill the twiddle tables from twr[r] = W_W^r and twc[r * sc] = W_H^r.
+template <typename S>
+__device__ __forceinline__ void rect_twiddles(float2* t, const float2* __restrict__ twr,
+                                              const float2* __restrict__ twc, int sc, unsigned tid) {
+    for (unsigned e = tid; e < (unsigned)S::TWS; e += S::NT) {
+        if (e < (unsigned)S::TWB) {
+            const unsigned a = e / (S::RA + 1), b = e % (S::RA + 1);
+            t[e] = twr[b < (unsigned)S::RA ? a * b : 0];
+        } else if (e < (unsigned)S::TWC) {
+            const unsigned q = e - S::TWB;
+            t[e] = twr[(q / S::RB) * (q % S::RB)];
+        } else if (e < (unsigned)S::TWD) {
+            const unsigned q = e - S::TWC;
+            t[e] = twc[(q / S::RC) * (q % S::RC) * sc];
+        } else {
+            const unsigned q = e - S::TWD, a = q / (S::RD + 1), b = q % (S::RD + 1);
+            t[e] = twc[b < (unsigned)S::RD ? a * b * sc : 0];
+        }
+    }
+}
+
+template <typename S>
+__device__ __forceinline__ unsigned rect_e1(unsigned r, unsigned c) {
+    return r * S::W + 2 * ((S::RB / 2) * (r % S::R1) + (r / S::R1) % (S::RB / 2)) + 32 * (r / S::R1) + c;
+}
+template <typename S>
+__device__ __forceinline__ unsigned rect_e2(unsigned r, unsigned c) {
+    return r * (S::W + 1) + c;
+}
+
 // Thread coordinates in each layout (tid in [0, NT)):
-//   A: y = tid / (P/2), j = tid % (P/2); holds x = 2j + q + P m     at v[8q + m]
-//   B: t = tid + i NT (i < TB): y = t % N, k1 = t / N; holds x0    at v[P i + x0]
-//   C: kx = tid % N, y0 = tid / N + i P/2 (i < TB);   holds m      at v[P i + m]
-//   D: jx = tid % (N/2), k1 = tid / (N/2); kx = 2jx + q; holds y0  at v[8q + y0]
-
-template <int N, bool INV>
-__device__ __forceinline__ void pass_A(float2 (&v)[16], const float2* __restrict__ tw, unsigned tid) {
-    constexpr int P = Res<N>::P;
-    const unsigned j = tid % (P / 2);
+//   A: y = tid / (RB/TA), j = tid % (RB/TA); holds x = TA j + q + RB m  at v[RA q + m]
+//   B: t = tid + i NT (i < TB): y = t % H, k1 = t / H; holds x0         at v[RB i + x0]
+//   C: kx = tid % W, y0 = tid / W + i YC (i < TC); holds m              at v[RC i + m]
+//   D: task q's modes (k1 + RC k2, kx) at v[RD q + k2]
+template <typename S>
+__device__ __forceinline__ void store_e1_a(float2* lds, const float2 (&v)[S::V], unsigned y, unsigned j) {
 #pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        dft_slice<8, INV>(v + 8 * q);
-        if (!INV) {
-            const float2* row = tw + Res<N>::TWA + 9 * (2 * j + q);
+    for (int k = 0; k < S::RA; ++k) {
+        if constexpr (S::TA == 2) st2(lds, rect_e1<S>(y, k * S::RB + 2 * j), v[k], v[S::RA + k]);
+        else lds[rect_e1<S>(y, k * S::RB + j)] = v[k];
+    }
+}
+template <typename S>
+__device__ __forceinline__ void load_e1_a(const float2* lds, float2 (&v)[S::V], unsigned y, unsigned j) {
 #pragma unroll
-            for (int k1 = 1; k1 < 8; ++k1) v[8 * q + k1] = twiddle<false>(v[8 * q + k1], row, k1);
-        }
+    for (int k = 0; k < S::RA; ++k) {
+        if constexpr (S::TA == 2) ld2(lds, rect_e1<S>(y, k * S::RB + 2 * j), v[k], v[S::RA + k]);
+        else v[k] = lds[rect_e1<S>(y, k * S::RB + j)];
     }
 }
 
-template <int N>
-__device__ __forceinline__ void store_E1_from_A(float2* lds, const float2 (&v)[16], unsigned tid) {
-    constexpr int P = Res<N>::P;
-    const unsigned y = tid / (P / 2), j = tid % (P / 2);
+template <typename S, typename D>
+__device__ __forceinline__ void rect_forward(float2 (&v)[S::V], float2* lds, const float2* __restrict__ tw,
+                                             unsigned tid, const D& dp) {
+    constexpr int RA = S::RA, RB = S::RB, RC = S::RC, RD = S::RD, H = S::H;
+    const unsigned ya = tid / (RB / S::TA), j = tid % (RB / S::TA);
+    // A
 #pragma unroll
-    for (int k1 = 0; k1 < 8; ++k1) st2(lds, e1<N>(y, k1 * P + 2 * j), v[k1], v[8 + k1]);
-}
-
-template <int N>
-__device__ __forceinline__ void load_A_from_E1(const float2* lds, float2 (&v)[16], unsigned tid) {
-    constexpr int P = Res<N>::P;
-    const unsigned y = tid / (P / 2), j = tid % (P / 2);
+    for (int q = 0; q < S::TA; ++q) {
+        dft_slice<RA, false>(v + RA * q);
+        const float2* row = tw + S::TWA + (RA + 1) * (S::TA * j + q);
 #pragma unroll
-    for (int k1 = 0; k1 < 8; ++k1) ld2(lds, e1<N>(y, k1 * P + 2 * j), v[k1], v[8 + k1]);
-}
-
-template <int N>
-__device__ __forceinline__ void load_B_from_E1(const float2* lds, float2 (&v)[16], unsigned tid) {
-    constexpr int P = Res<N>::P, NT = Res<N>::NT, TB = Res<N>::TB;
-#pragma unroll
-    for (int i = 0; i < TB; ++i) {
-        const unsigned t = tid + i * NT, y = t % N, k1 = t / N;
-#pragma unroll
-        for (int x0 = 0; x0 < P; x0 += 2) ld2(lds, e1<N>(y, k1 * P + x0), v[P * i + x0], v[P * i + x0 + 1]);
+        for (int k = 1; k < RA; ++k) v[RA * q + k] = twiddle<false>(v[RA * q + k], row, k);
     }
-}
-
-template <int N>
-__device__ __forceinline__ void store_E1_from_B(float2* lds, const float2 (&v)[16], unsigned tid) {
-    constexpr int P = Res<N>::P, NT = Res<N>::NT, TB = Res<N>::TB;
-#pragma unroll
-    for (int i = 0; i < TB; ++i) {
-        const unsigned t = tid + i * NT, y = t % N, k1 = t / N;
-#pragma unroll
-        for (int x0 = 0; x0 < P; x0 += 2) st2(lds, e1<N>(y, k1 * P + x0), v[P * i + x0], v[P * i + x0 + 1]);
-    }
-}
-
-// pass B: forward radix-P over x0 -> k2 (no twiddle after);
-// inverse: radix-P over k2 -> x0, then twiddle conj W_N^(x0 k1).
-template <int N, bool INV>
-__device__ __forceinline__ void pass_B(float2 (&v)[16], const float2* __restrict__ tw, unsigned tid) {
-    constexpr int P = Res<N>::P, NT = Res<N>::NT, TB = Res<N>::TB;
-#pragma unroll
-    for (int i = 0; i < TB; ++i) {
-        dft_slice<P, INV>(v + P * i);
-        if (INV) {
-            const float2* row = tw + Res<N>::TWB + P * ((tid + i * NT) / N);
-#pragma unroll
-            for (int x0 = 1; x0 < P; ++x0) v[P * i + x0] = twiddle<true>(v[P * i + x0], row, x0);
-        }
-    }
-}
-
-template <int N>
-__device__ __forceinline__ void store_E2_from_B(float2* lds, const float2 (&v)[16], unsigned tid) {
-    constexpr int P = Res<N>::P, NT = Res<N>::NT, TB = Res<N>::TB;
-#pragma unroll
-    for (int i = 0; i < TB; ++i) {
-        const unsigned t = tid + i * NT, y = t % N, k1 = t / N;
-#pragma unroll
-        for (int k2 = 0; k2 < P; ++k2) lds[e2<N>(y, k1 + 8 * k2)] = v[P * i + k2];
-    }
-}
-
-template <int N>
-__device__ __forceinline__ void load_B_from_E2(const float2* lds, float2 (&v)[16], unsigned tid) {
-    constexpr int P = Res<N>::P, NT = Res<N>::NT, TB = Res<N>::TB;
-#pragma unroll
-    for (int i = 0; i < TB; ++i) {
-        const unsigned t = tid + i * NT, y = t % N, k1 = t / N;
-#pragma unroll
-        for (int k2 = 0; k2 < P; ++k2) v[P * i + k2] = lds[e2<N>(y, k1 + 8 * k2)];
-    }
-}
-
-template <int N>
-__device__ __forceinline__ void load_C_from_E2(const float2* lds, float2 (&v)[16], unsigned tid) {
-    constexpr int P = Res<N>::P, TB = Res<N>::TB;
-    const unsigned kx = tid % N;
-#pragma unroll
-    for (int i = 0; i < TB; ++i) {
-        const unsigned y0 = tid / N + i * (P / 2);
-#pragma unroll
-        for (int m = 0; m < P; ++m) v[P * i + m] = lds[e2<N>(y0 + 8 * m, kx)];
-    }
-}
-
-template <int N>
-__device__ __forceinline__ void store_E2_from_C(float2* lds, const float2 (&v)[16], unsigned tid) {
-    constexpr int P = Res<N>::P, TB = Res<N>::TB;
-    const unsigned kx = tid % N;
-#pragma unroll
-    for (int i = 0; i < TB; ++i) {
-        const unsigned y0 = tid / N + i * (P / 2);
-#pragma unroll
-        for (int m = 0; m < P; ++m) lds[e2<N>(y0 + 8 * m, kx)] = v[P * i + m];
-    }
-}
-
-// pass C: forward radix-P over m -> k1, then twiddle W_N^(y0 k1);
-// inverse: radix-P over k1 -> m (the twiddle was applied in D').
-template <int N, bool INV>
-__device__ __forceinline__ void pass_C(float2 (&v)[16], const float2* __restrict__ tw, unsigned tid) {
-    constexpr int P = Res<N>::P, TB = Res<N>::TB;
-#pragma unroll
-    for (int i = 0; i < TB; ++i) {
-        dft_slice<P, INV>(v + P * i);
-        if (!INV) {
-            const float2* row = tw + Res<N>::TWC + P * (tid / N + i * (P / 2));
-#pragma unroll
-            for (int k1 = 1; k1 < P; ++k1) v[P * i + k1] = twiddle<false>(v[P * i + k1], row, k1);
-        }
-    }
-}
-
-template <int N>
-__device__ __forceinline__ void store_E3_from_C(float2* lds, const float2 (&v)[16], unsigned tid) {
-    constexpr int P = Res<N>::P, TB = Res<N>::TB;
-    const unsigned kx = tid % N;
-#pragma unroll
-    for (int i = 0; i < TB; ++i) {
-        const unsigned y0 = tid / N + i * (P / 2);
-#pragma unroll
-        for (int k1 = 0; k1 < P; ++k1) lds[e3<N>(k1 * 8 + y0, kx)] = v[P * i + k1];
-    }
-}
-
-template <int N>
-__device__ __forceinline__ void load_C_from_E3(const float2* lds, float2 (&v)[16], unsigned tid) {
-    constexpr int P = Res<N>::P, TB = Res<N>::TB;
-    const unsigned kx = tid % N;
-#pragma unroll
-    for (int i = 0; i < TB; ++i) {
-        const unsigned y0 = tid / N + i * (P / 2);
-#pragma unroll
-        for (int k1 = 0; k1 < P; ++k1) v[P * i + k1] = lds[e3<N>(k1 * 8 + y0, kx)];
-    }
-}
-
-// (8-byte accesses: at pitch N + 1 a pair of columns is not 16-byte aligned)
-template <int N>
-__device__ __forceinline__ void load_D_from_E3(const float2* lds, float2 (&v)[16], unsigned tid) {
-    const unsigned jx = tid % (N / 2), k1 = tid / (N / 2);
-#pragma unroll
-    for (int y0 = 0; y0 < 8; ++y0) {
-        const unsigned i = e3<N>(k1 * 8 + y0, 2 * jx);
-        v[y0] = lds[i];
-        v[8 + y0] = lds[i + 1];
-    }
-}
-
-template <int N>
-__device__ __forceinline__ void store_E3_from_D(float2* lds, const float2 (&v)[16], unsigned tid) {
-    const unsigned jx = tid % (N / 2), k1 = tid / (N / 2);
-#pragma unroll
-    for (int y0 = 0; y0 < 8; ++y0) {
-        const unsigned i = e3<N>(k1 * 8 + y0, 2 * jx);
-        lds[i] = v[y0];
-        lds[i + 1] = v[8 + y0];
-    }
-}
-
-// pass D: forward radix-8 over y0 -> k2 (ky = k1 + P k2);
-// inverse: radix-8 over k2 -> y0, then twiddle conj W_N^(y0 k1).
-template <int N, bool INV>
-__device__ __forceinline__ void pass_D(float2 (&v)[16], const float2* __restrict__ tw, unsigned tid) {
-    const float2* row = tw + Res<N>::TWD + 8 * (tid / (N / 2));
-#pragma unroll
-    for (int q = 0; q < 2; ++q) {
-        dft_slice<8, INV>(v + 8 * q);
-        if (INV) {
-#pragma unroll
-            for (int y0 = 1; y0 < 8; ++y0) v[8 * q + y0] = twiddle<true>(v[8 * q + y0], row, y0);
-        }
-    }
-}
-
-// tw: the four twiddle tables in LDS (fill_twiddle_tables).
-template <int N>
-__device__ __forceinline__ void forward_fft(float2 (&v)[16], float2* lds, const float2* __restrict__ tw, unsigned tid) {
-    pass_A<N, false>(v, tw, tid);
-    store_E1_from_A<N>(lds, v, tid);
+    store_e1_a<S>(lds, v, ya, j);
     __syncthreads();
-    load_B_from_E1<N>(lds, v, tid);
+    // B
+#pragma unroll
+    for (int i = 0; i < S::TB; ++i) {
+        const unsigned t = tid + i * S::NT, y = t % H, k1 = t / H;
+#pragma unroll
+        for (int x = 0; x < RB; x += 2) ld2(lds, rect_e1<S>(y, k1 * RB + x), v[RB * i + x], v[RB * i + x + 1]);
+    }
     __syncthreads();
-    pass_B<N, false>(v, tw, tid);
-    store_E2_from_B<N>(lds, v, tid);
+#pragma unroll
+    for (int i = 0; i < S::TB; ++i) dft_slice<RB, false>(v + RB * i);
+#pragma unroll
+    for (int i = 0; i < S::TB; ++i) {
+        const unsigned t = tid + i * S::NT, y = t % H, k1 = t / H;
+#pragma unroll
+        for (int k = 0; k < RB; ++k) lds[rect_e2<S>(y, k1 + RA * k)] = v[RB * i + k];
+    }
     __syncthreads();
-    load_C_from_E2<N>(lds, v, tid);
-    pass_C<N, false>(v, tw, tid);
-    store_E3_from_C<N>(lds, v, tid);  // the addresses this thread read from E2
+    // C
+    const unsigned kx = tid % S::W, yc = tid / S::W;
+#pragma unroll
+    for (int i = 0; i < S::TC; ++i)
+#pragma unroll
+        for (int m = 0; m < RC; ++m) v[RC * i + m] = lds[rect_e2<S>(yc + i * S::YC + RD * m, kx)];
+#pragma unroll
+    for (int i = 0; i < S::TC; ++i) {
+        dft_slice<RC, false>(v + RC * i);
+        const float2* row = tw + S::TWC + RC * (yc + i * S::YC);
+#pragma unroll
+        for (int k = 1; k < RC; ++k) v[RC * i + k] = twiddle<false>(v[RC * i + k], row, k);
+#pragma unroll
+        for (int k = 0; k < RC; ++k) lds[rect_e2<S>(RD * k + yc + i * S::YC, kx)] = v[RC * i + k];
+    }
     __syncthreads();
-    load_D_from_E3<N>(lds, v, tid);
-    pass_D<N, false>(v, tw, tid);
+    // D
+#pragma unroll
+    for (int y = 0; y < RD; ++y)
+#pragma unroll
+        for (int q = 0; q < S::TD; ++q) v[RD * q + y] = lds[rect_e2<S>(RD * dp.k1(q) + y, dp.kx(q))];
+#pragma unroll
+    for (int q = 0; q < S::TD; ++q) dft_slice<RD, false>(v + RD * q);
 }
 
-template <int N>
-__device__ __forceinline__ void inverse_fft(float2 (&v)[16], float2* lds, const float2* __restrict__ tw, unsigned tid) {
-    pass_D<N, true>(v, tw, tid);
-    store_E3_from_D<N>(lds, v, tid);
+template <typename S, typename D>
+__device__ __forceinline__ void rect_inverse(float2 (&v)[S::V], float2* lds, const float2* __restrict__ tw,
+                                             unsigned tid, const D& dp) {
+    constexpr int RA = S::RA, RB = S::RB, RC = S::RC, RD = S::RD, H = S::H;
+    // D
+#pragma unroll
+    for (int q = 0; q < S::TD; ++q) {
+        dft_slice<RD, true>(v + RD * q);
+        const float2* row = tw + S::TWD + (RD + 1) * dp.k1(q);
+#pragma unroll
+        for (int y = 1; y < RD; ++y) v[RD * q + y] = twiddle<true>(v[RD * q + y], row, y);
+    }
+#pragma unroll
+    for (int y = 0; y < RD; ++y)
+#pragma unroll
+        for (int q = 0; q < S::TD; ++q) lds[rect_e2<S>(RD * dp.k1(q) + y, dp.kx(q))] = v[RD * q + y];
     __syncthreads();
-    load_C_from_E3<N>(lds, v, tid);
-    pass_C<N, true>(v, tw, tid);
-    store_E2_from_C<N>(lds, v, tid);  // the addresses this thread read from E3
+    // C
+    const unsigned kx = tid % S::W, yc = tid / S::W;
+#pragma unroll
+    for (int i = 0; i < S::TC; ++i)
+#pragma unroll
+        for (int k = 0; k < RC; ++k) v[RC * i + k] = lds[rect_e2<S>(RD * k + yc + i * S::YC, kx)];
+#pragma unroll
+    for (int i = 0; i < S::TC; ++i) {
+        dft_slice<RC, true>(v + RC * i);
+#pragma unroll
+        for (int m = 0; m < RC; ++m) lds[rect_e2<S>(yc + i * S::YC + RD * m, kx)] = v[RC * i + m];
+    }
     __syncthreads();
-    load_B_from_E2<N>(lds, v, tid);
+    // B
+#pragma unroll
+    for (int i = 0; i < S::TB; ++i) {
+        const unsigned t = tid + i * S::NT, y = t % H, k1 = t / H;
+#pragma unroll
+        for (int k = 0; k < RB; ++k) v[RB * i + k] = lds[rect_e2<S>(y, k1 + RA * k)];
+    }
     __syncthreads();
-    pass_B<N, true>(v, tw, tid);
-    store_E1_from_B<N>(lds, v, tid);
+#pragma unroll
+    for (int i = 0; i < S::TB; ++i) {
+        const unsigned t = tid + i * S::NT, y = t % H, k1 = t / H;
+        dft_slice<RB, true>(v + RB * i);
+        const float2* row = tw + S::TWB + RB * k1;
+#pragma unroll
+        for (int x = 1; x < RB; ++x) v[RB * i + x] = twiddle<true>(v[RB * i + x], row, x);
+#pragma unroll
+        for (int x = 0; x < RB; x += 2) st2(lds, rect_e1<S>(y, k1 * RB + x), v[RB * i + x], v[RB * i + x + 1]);
+    }
     __syncthreads();
-    load_A_from_E1<N>(lds, v, tid);
-    pass_A<N, true>(v, tw, tid);
+    // A
+    load_e1_a<S>(lds, v, tid / (RB / S::TA), tid % (RB / S::TA));
+#pragma unroll
+    for (int q = 0; q < S::TA; ++q) dft_slice<RA, true>(v + RA * q);
 }
+
+// c ? a : b by value (the conditional operator on array elements selects their
+// addresses, which would put the arrays in scratch memory).
+__device__ __forceinline__ float2 pick(bool c, float2 a, float2 b) { return make_float2(c ? a.x : b.x, c ? a.y : b.y); }
+
+// A Fourier step on layout D that combines every mode with its mirror:
+//   mirror_put, barrier, mirror_step, barrier, mirror_get
+// with `sz` 8 RD elements of LDS.  f.pair(k2, ky, kx, za, zb, sa, sb) takes
+// Z(k) and Z(-k) of task a's mode k = (ky, kx), ky = k1a + RC k2, and gives both
+// new values.  The modes of the tasks that mirror themselves go through sz to
+// 4 RD threads, one mode each (left to the two threads that hold them, they
+// would be 2 RD modes one after the other while every other wave waits at the
+// barrier: 2 us of a 128^2 mass-mapping sweep); f.single(ky, kx, z, zm) gives the
+// new value of one of them.
+template <typename S>
+__device__ __forceinline__ void mirror_put(const float2 (&v)[S::V], const DPair& dp, float2* sz) {
+    if (dp.self) {
+        float2* o = sz + (dp.zero ? 0 : 2 * S::RD);  // tasks (0, 0), (W/2, 0), (0, RC/2), (W/2, RC/2)
+#pragma unroll
+        for (int e = 0; e < S::V; ++e) o[e] = v[e];
+    }
+}
+template <typename S>
+__device__ __forceinline__ void mirror_get(float2 (&v)[S::V], const DPair& dp, const float2* sz) {
+    if (dp.self) {
+        const float2* o = sz + 4 * S::RD + (dp.zero ? 0 : 2 * S::RD);
+#pragma unroll
+        for (int e = 0; e < S::V; ++e) v[e] = o[e];
+    }
+}
+template <typename S, typename F>
+__device__ __forceinline__ void mirror_step(float2 (&v)[S::V], const DPair& dp, unsigned tid, float2* sz, F&& f) {
+    constexpr int RC = S::RC, RD = S::RD;
+    static_assert(S::NT >= 4 * RD, "one thread per self-mirrored mode");
+    float2 om[RD];
+#pragma unroll
+    for (int k2 = 0; k2 < RD; ++k2) {
+        __builtin_amdgcn_sched_barrier(0);
+        const float2 zb = pick(dp.zero, v[RD + (RD - k2) % RD], v[2 * RD - 1 - k2]);
+        float2 sa;
+        f.pair(k2, dp.k1a + RC * k2, dp.kxa, v[k2], zb, sa, om[k2]);
+        v[k2] = sa;
+    }
+#pragma unroll
+    for (int k2 = 0; k2 < RD; ++k2) v[RD + k2] = pick(dp.zero, om[(RD - k2) % RD], om[RD - 1 - k2]);
+    if (tid < 4 * RD) {
+        __builtin_amdgcn_sched_barrier(0);
+        const unsigned k2 = tid % RD, task = tid / RD;
+        const unsigned m = task < 2 ? (RD - k2) % RD : RD - 1 - k2;
+        sz[4 * RD + tid] = f.single((task < 2 ? 0 : RC / 2) + RC * k2, task % 2 ? S::W / 2 : 0, sz[tid],
+                                    sz[tid - k2 + m]);
+    }
+}
+
+// Square fields with 16 values per thread.
+template <int N> struct SquareShape;
+template <> struct SquareShape<32> { using type = Rect<32, 32, 16, 8, 4, 4, 8>; };
+template <> struct SquareShape<64> { using type = Rect<64, 64, 16, 8, 8, 8, 8>; };
+template <> struct SquareShape<128> { using type = Rect<128, 128, 16, 8, 16, 16, 8>; };
 
 }  // namespace
 

@@ -16,7 +16,7 @@
 // field is transformed back.
 #include "mf_device.hpp"
 #include "mf_resident.hpp"
-#include "mf_rect_fft.hpp"
+#include "mf_resident_fft.hpp"
 #include "mf_shear.hpp"
 
 namespace mf {

@@ -13,7 +13,7 @@
 //     E' = f_+ E + f_- W O,   O' = f_- conj(W) E + f_+ O,
 // and, since E = (Z(k) + conj Z(-k))/2 and O = (Z(k) - conj Z(-k))/2i,
 //     S(k) = E' + i O' = (f_+ - f_- sin th) Z(k) + i f_- cos th conj Z(-k).
-// k and -k sit in one thread (mf_rect_fft.hpp), so the step takes no exchange.
+// k and -k sit in one thread (mf_resident_fft.hpp), so the step takes no exchange.
 //
 // 16 complex values per thread at 128^2 (512 threads: two waves per SIMD with
 // 256 VGPRs), 8 at 64^2 and 32^2 (256 and 64 threads).  The registers hold the
@@ -28,7 +28,7 @@
 // per SIMD; the rest is latency (LDS exchanges behind block barriers).
 #include "mf_device.hpp"
 #include "mf_resident.hpp"
-#include "mf_rect_fft.hpp"
+#include "mf_resident_fft.hpp"
 
 namespace mf {
 

@@ -9,7 +9,7 @@
 //     S(k) = f_+ Z(k) + f_- conj(Z(-k)) + w_+ eta(k) + w_- conj(eta(-k))
 // gives chain A (real part of the inverse transform) the update f_A Z_A + w_A
 // noise and chain B (imaginary part) f_B Z_B + w_B noise, exactly.  The
-// transform leaves k and -k in one thread (mf_rect_fft.hpp); eta goes through
+// transform leaves k and -k in one thread (mf_resident_fft.hpp); eta goes through
 // LDS, since a Philox call's two modes sit in neighbouring lanes.
 //
 // The amplitudes given the signal are inverse-gamma: theta_b = (2 beta_0 +
@@ -19,7 +19,7 @@
 // freedom, counter word 1 = the global iteration).
 #include "mf_device.hpp"
 #include "mf_resident.hpp"
-#include "mf_rect_fft.hpp"
+#include "mf_resident_fft.hpp"
 #include "mf_spectrum.hpp"
 
 namespace mf {

@@ -116,11 +116,6 @@ __device__ __forceinline__ void row_forward(float2* buf, unsigned lane, const fl
     }
 }
 
-// Value of the neighbouring lane (lane ^ 1) in one DPP move (quad_perm 1,0,3,2).
-__device__ __forceinline__ float swap_lanes(float v) {
-    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, false));
-}
-
 // Column tiles of the mirror-paired column kernels (L >= 256): TC slot columns
 // of L rows, slot c of column col_of(c), each its own LDS segment of SEG.
 // The first forward radix-16 pass reads its inputs straight from HBM (a wave
