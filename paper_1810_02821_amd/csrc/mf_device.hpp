@@ -17,6 +17,9 @@ __device__ __forceinline__ float2 cmul(float2 a, float2 b) {
 __device__ __forceinline__ float2 cmulc(float2 a, float2 b) {
     return make_float2(fmaf(a.x, b.x, a.y * b.y), fmaf(a.y, b.x, -a.x * b.y));
 }
+// c ? a : b by value (the conditional operator on array elements selects their
+// addresses, which would put the arrays in scratch memory).
+__device__ __forceinline__ float2 pick(bool c, float2 a, float2 b) { return make_float2(c ? a.x : b.x, c ? a.y : b.y); }
 __device__ __forceinline__ float2 cscale(float2 a, float s) { return make_float2(a.x * s, a.y * s); }
 // multiply by -i (forward) or +i (inverse)
 template <bool INV> __device__ __forceinline__ float2 mul_mi(float2 a) {
@@ -276,6 +279,33 @@ __device__ __forceinline__ unsigned xcd_block(unsigned b, unsigned nb) {
 // Value of the neighbouring lane (lane ^ 1) in one DPP move (quad_perm 1,0,3,2).
 __device__ __forceinline__ float swap_lanes(float v) {
     return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), 0xB1, 0xF, 0xF, false));
+}
+
+// ------------------------------------------------------- real-field filter --
+// p / (p + T) to FP32 rounding: one Newton step on the reciprocal and one
+// correction with the exact remainder, the rounding of p + T included.
+__device__ __forceinline__ float wiener_f(float p, float T) {
+    const float den = p + T;
+    const float big = fmaxf(p, T), small = fminf(p, T);
+    const float lo = small - (den - big);  // p + T = den + lo exactly
+    float r = __builtin_amdgcn_rcpf(den);
+    r = fmaf(fmaf(-den, r, 1.0f), r, r);
+    const float q = p * r;
+    return fmaf(fmaf(-lo, q, fmaf(-den, q, p)), r, q);
+}
+
+// A real field folded to half a complex field z = t_even + i t_odd (alternate
+// rows or columns): with f(k), f(k + M) the filter at the two modes that share
+// one of the folded transform's, th the twiddle (cos, -sin) of the fold and
+// f_+- = (f(k) +- f(k + M))/2, the filtered transform is S(k) = a Z(k) + i b
+// conj Z(-k), a = f_+ - f_- sin, b = f_- cos; at -k it is m Z(-k) + i b conj
+// Z(k), m = f_+ + f_- sin.  Everything times 2 scale.
+struct RealFilter {
+    float a, m, b;
+};
+__device__ __forceinline__ RealFilter real_filter(float p0, float p1, float T, float2 th, float scale) {
+    const float f0 = wiener_f(p0, T), f1 = wiener_f(p1, T), lo = 1.0f + th.y, hi = 1.0f - th.y;
+    return {fmaf(f0, lo, f1 * hi) * scale, fmaf(f0, hi, f1 * lo) * scale, (f0 - f1) * th.x * scale};
 }
 
 // -------------------------------------------------------- normal variates --

@@ -16,6 +16,7 @@
 #include "../../include/mf.h"
 #include "mf_kernels.hpp"
 #include "mf_resident.hpp"
+#include "mf_real.hpp"
 #include "mf_spectrum.hpp"
 #include "mf_shear.hpp"
 #include "mf_static.hpp"
@@ -489,13 +490,138 @@ mf_status put_items(mf_plan p, const std::vector<mf::ItemDev>& it, size_t slot, 
     return MF_OK;
 }
 
+mf_status copy_class_real(mf_plan p, const std::vector<int>& pids, int H, int W, float* out, hipStream_t s);
+
+// Convergence phase of a streamed solve: sweeps at the last level over a
+// shrinking list of items until each residual meets the tolerance.  `total`
+// sweeps have run (`first`: none); use(list, n) sets the items of the following
+// sweeps, sweep(save, check) runs one (and counts it in total), finish(list, n)
+// writes the listed items' results.
+template <typename Use, typename Sweep, typename Finish>
+mf_status converge_class(mf_plan p, const std::vector<mf::ItemDev>& items, int H, const mf_schedule* sch, int& total,
+                         const bool& first, std::vector<double>& bnorm2, std::vector<mf_info>& info, hipStream_t s,
+                         Use&& use, Sweep&& sweep, Finish&& finish) {
+    const int n_items = (int)items.size(), levels_total = total;
+    const double lam = sch->lambda[sch->n_levels - 1];
+    const double* partials = p->partials.as<double>();
+    std::vector<double> part((size_t)n_items * H);
+    std::vector<mf::ItemDev> live = items;
+    mf::ItemDev* d_live = p->items.as<mf::ItemDev>();
+    mf_status st = MF_OK;
+    while (total < sch->max_sweeps && !live.empty()) {
+        const int c = total + 1;  // count after this sweep
+        const bool check = (c % sch->check_every == 0) && (c - 1 >= levels_total + 1);
+        const bool save = ((c + 1) % sch->check_every == 0);
+        if ((st = sweep(save, check)) != MF_OK) return st;
+        if (!check) continue;
+        const int n = (int)live.size();
+        MF_HIP(hipMemcpyAsync(part.data(), partials, (size_t)n * H * sizeof(double), hipMemcpyDeviceToHost, s));
+        MF_HIP(hipStreamSynchronize(s));
+        std::vector<mf::ItemDev> conv, keep;
+        for (int i = 0; i < n; ++i) {
+            double acc = 0;  // row partials are indexed y * n_items + item
+            for (int y = 0; y < H; ++y) acc += part[(size_t)y * n + i];
+            const int pid = live[i].prob;
+            const double T = lam * p->probs[pid].tau;
+            const double r = bnorm2[pid] == 0.0 ? 0.0 : std::sqrt(acc) / (T * std::sqrt(bnorm2[pid]));
+            info[pid].residual = r;
+            info[pid].sweeps = total;
+            if (r <= sch->tol) {
+                info[pid].converged = 1;
+                conv.push_back(live[i]);
+            } else if (!std::isfinite(r)) {
+                info[pid].converged = -1;  // non-finite: stop iterating this problem
+                conv.push_back(live[i]);
+            } else {
+                keep.push_back(live[i]);
+            }
+        }
+        if (!conv.empty()) {
+            // finish converged items with the inverse row pass and drop them
+            mf::ItemDev* d_conv = nullptr;
+            if ((st = put_items(p, conv, (size_t)n_items, s, &d_conv)) != MF_OK) return st;
+            if ((st = finish(d_conv, (int)conv.size())) != MF_OK) return st;
+            live = keep;
+            if (!live.empty()) {
+                if ((st = put_items(p, live, 0, s, &d_live)) != MF_OK) return st;
+                use(d_live, (int)live.size());
+            }
+            MF_HIP(hipStreamSynchronize(s));
+        }
+    }
+    for (auto& it : live) info[it.prob].sweeps = total;
+    if (!live.empty() && !first) return finish(d_live, (int)live.size());
+    return MF_OK;
+}
+
+// solve_class on the real-field kernels; `sa` carries the work list.
+mf_status solve_class_real(mf_plan p, const std::vector<int>& pids, int H, int W, const mf::SweepArgs& sa,
+                           const float* src, int src_kind, const mf_schedule* sch, const float* s_init, float* out,
+                           std::vector<double>& bnorm2, std::vector<mf_info>& info, hipStream_t s) {
+    mf::RealArgs a{};
+    a.items = sa.items;
+    a.n_items = sa.n_items;
+    while ((1 << a.log_h) < H) ++a.log_h;
+    while ((1 << a.log_w) < W) ++a.log_w;
+    a.src_kind = src_kind;
+    a.field = p->field.as<float2>();
+    a.src = src;
+    a.nbar = p->d_nbar;
+    a.nPt = p->d_nPt;
+    a.tw_w = p->d_tw.at(W);
+    a.tw_h = p->d_tw.at(H);
+    a.s_init = s_init;
+    a.s_out = out;
+    a.t_save = p->t_save.as<float2>();
+    a.partials = p->partials.as<double>();
+    bool first = true;
+    int total = 0;
+    auto sweep = [&](double lam, bool save, bool check) -> mf_status {
+        a.lambda = (float)lam;
+        a.save_t = save;
+        a.check_t = check;
+        MF_HIP(mf::launch_real_row(first ? mf::kRowFwd : mf::kRowInvFwd, a, s));
+        MF_HIP(mf::launch_real_col(a, s));
+        first = false;
+        ++total;
+        return MF_OK;
+    };
+    auto finish = [&](const mf::ItemDev* d_it, int n) -> mf_status {
+        mf::RealArgs b = a;
+        b.items = d_it;
+        b.n_items = n;
+        MF_HIP(mf::launch_real_row(mf::kRowInv, b, s));
+        return MF_OK;
+    };
+    mf_status st = MF_OK;
+    for (int j = 0; j < sch->n_levels; ++j)
+        for (int k = 0; k < sch->sweeps[j]; ++k)
+            if ((st = sweep(sch->lambda[j], false, false)) != MF_OK) return st;
+    const int n_items = (int)pids.size();
+    for (int i = 0; i < n_items; ++i) info[pids[i]] = {total, sch->tol > 0 ? 0 : 1, std::nan("")};
+    if (sch->tol > 0) {
+        std::vector<mf::ItemDev> items(n_items);  // host copy for the residual bookkeeping
+        for (int i = 0; i < n_items; ++i) items[i] = item_of(p, pids[i], 0, p->probs[pids[i]].pix_off);
+        st = converge_class(
+            p, items, H, sch, total, first, bnorm2, info, s, [&](mf::ItemDev* d_it, int n) { a.items = d_it; a.n_items = n; },
+            [&](bool save, bool check) { return sweep(sch->lambda[sch->n_levels - 1], save, check); }, finish);
+        if (st != MF_OK) return st;
+    } else if (!first) {
+        if ((st = finish(a.items, a.n_items)) != MF_OK) return st;
+    }
+    if (!first) return MF_OK;  // the last row kernels wrote `out`
+    MF_HIP(mf::launch_load_real(W, H, sa, s_init, s));  // no sweep: the start
+    return copy_class_real(p, pids, H, W, out, s);
+}
+
 // -------------------------------------------------------------------------
 // Deterministic solve (Wiener filter or adjoint) on the streamed kernels for
-// the problems of one size class.  Field layout: one complex field per problem
-// at field_off = pix_off (float2 units).
+// the problems of one size class, result to `out`.  Field layout: one complex
+// field per problem at field_off = pix_off (float2 units); on the real-field
+// kernels (powers of two from 256) half of one, at pix_off / 2.
 // -------------------------------------------------------------------------
 mf_status solve_class(mf_plan p, const std::vector<int>& pids, int H, int W, const float* src, int src_kind,
-                      const mf_schedule* sch, const float* s_init, std::vector<double>& bnorm2,
+                      const mf_schedule* sch, const float* s_init, float* out, std::vector<double>& bnorm2,
                       std::vector<mf_info>& info, hipStream_t s) {
     const int n_items = (int)pids.size();
     std::vector<mf::ItemDev> items(n_items);  // host copy for the residual bookkeeping
@@ -515,6 +641,8 @@ mf_status solve_class(mf_plan p, const std::vector<int>& pids, int H, int W, con
     a.real_only = 1;
     a.t_save = p->t_save.as<float2>();
     a.partials = p->partials.as<double>();
+    if (mf::real_solve_supported(H, W))
+        return solve_class_real(p, pids, H, W, a, src, src_kind, sch, s_init, out, bnorm2, info, s);
     MF_HIP(mf::launch_load_real(W, H, a, s_init, s));
 
     bool first = true;
@@ -533,68 +661,23 @@ mf_status solve_class(mf_plan p, const std::vector<int>& pids, int H, int W, con
     for (int j = 0; j < sch->n_levels; ++j)
         for (int k = 0; k < sch->sweeps[j]; ++k)
             if ((st = sweep(sch->lambda[j], false, false)) != MF_OK) return st;
-    const int levels_total = total;
-    std::vector<int> done(n_items, 0);
     for (int i = 0; i < n_items; ++i) info[pids[i]] = {total, sch->tol > 0 ? 0 : 1, std::nan("")};
-    if (sch->tol > 0) {
-        const double lam = sch->lambda[sch->n_levels - 1];
-        std::vector<double> part((size_t)n_items * H);
-        int remaining = n_items;
-        std::vector<mf::ItemDev> live = items;
-        while (total < sch->max_sweeps && remaining > 0) {
-            const int c = total + 1;  // count after this sweep
-            const bool check = (c % sch->check_every == 0) && (c - 1 >= levels_total + 1);
-            const bool save = ((c + 1) % sch->check_every == 0);
-            if ((st = sweep(lam, save, check)) != MF_OK) return st;
-            if (!check) continue;
-            MF_HIP(hipMemcpyAsync(part.data(), a.partials, (size_t)a.n_items * H * sizeof(double),
-                                  hipMemcpyDeviceToHost, s));
-            MF_HIP(hipStreamSynchronize(s));
-            std::vector<mf::ItemDev> conv, keep;
-            for (int i = 0; i < a.n_items; ++i) {
-                double acc = 0;  // row partials are indexed y * n_items + item
-                for (int y = 0; y < H; ++y) acc += part[(size_t)y * a.n_items + i];
-                const int pid = live[i].prob;
-                const double T = lam * p->probs[pid].tau;
-                const double r = bnorm2[pid] == 0.0 ? 0.0 : std::sqrt(acc) / (T * std::sqrt(bnorm2[pid]));
-                info[pid].residual = r;
-                info[pid].sweeps = total;
-                if (r <= sch->tol) {
-                    info[pid].converged = 1;
-                    conv.push_back(live[i]);
-                } else if (!std::isfinite(r)) {
-                    info[pid].converged = -1;  // non-finite: stop iterating this problem
-                    conv.push_back(live[i]);
-                } else {
-                    keep.push_back(live[i]);
-                }
-            }
-            if (!conv.empty()) {
-                // finish converged items with the inverse row pass and drop them
-                mf::ItemDev* d_conv = nullptr;
-                if ((st = put_items(p, conv, (size_t)n_items, s, &d_conv)) != MF_OK) return st;
-                mf::SweepArgs b = a;
-                b.items = d_conv;
-                b.n_items = (int)conv.size();
-                MF_HIP(mf::launch_row(W, H, mf::kRowInv, b, s));
-                remaining -= (int)conv.size();
-                live = keep;
-                if (!live.empty()) {
-                    if ((st = put_items(p, live, 0, s, &d_items)) != MF_OK) return st;
-                }
-                a.items = d_items;
-                a.n_items = (int)live.size();
-                MF_HIP(hipStreamSynchronize(s));
-            }
-        }
-        for (auto& it : live) info[it.prob].sweeps = total;
-        if (!live.empty() && !first) {
-            MF_HIP(mf::launch_row(W, H, mf::kRowInv, a, s));
-        }
+    auto finish = [&](mf::ItemDev* d_it, int n) -> mf_status {  // the inverse row pass of the listed items
+        mf::SweepArgs b = a;
+        b.items = d_it;
+        b.n_items = n;
+        MF_HIP(mf::launch_row(W, H, mf::kRowInv, b, s));
         return MF_OK;
+    };
+    if (sch->tol > 0) {
+        st = converge_class(
+            p, items, H, sch, total, first, bnorm2, info, s, [&](mf::ItemDev* d_it, int n) { a.items = d_it; a.n_items = n; },
+            [&](bool save, bool check) { return sweep(sch->lambda[sch->n_levels - 1], save, check); }, finish);
+        if (st != MF_OK) return st;
+    } else if (!first) {
+        if ((st = finish(d_items, n_items)) != MF_OK) return st;
     }
-    if (!first) MF_HIP(mf::launch_row(W, H, mf::kRowInv, a, s));
-    return MF_OK;
+    return copy_class_real(p, pids, H, W, out, s);
 }
 
 // Workspaces of the deterministic solves, the adjoint, the band reductions
@@ -916,8 +999,7 @@ mf_status run_solve(mf_plan p, const float* src, int src_kind, const mf_schedule
             if (st != MF_OK) return st;
             continue;
         }
-        if ((st = solve_class(p, kv.second, H, W, src, src_kind, sch, s_init, bn, info, s)) != MF_OK) return st;
-        if ((st = copy_class_real(p, kv.second, H, W, out, s)) != MF_OK) return st;
+        if ((st = solve_class(p, kv.second, H, W, src, src_kind, sch, s_init, out, bn, info, s)) != MF_OK) return st;
     }
     bool all = true, finite = true;
     for (auto& i : info) {

@@ -306,10 +306,6 @@ __device__ __forceinline__ void rect_inverse(float2 (&v)[S::V], float2* lds, con
     for (int q = 0; q < S::TA; ++q) dft_slice<RA, true>(v + RA * q);
 }
 
-// c ? a : b by value (the conditional operator on array elements selects their
-// addresses, which would put the arrays in scratch memory).
-__device__ __forceinline__ float2 pick(bool c, float2 a, float2 b) { return make_float2(c ? a.x : b.x, c ? a.y : b.y); }
-
 // A Fourier step on layout D that combines every mode with its mirror:
 //   mirror_put, barrier, mirror_step, barrier, mirror_get
 // with `sz` 8 RD elements of LDS.  f.pair(k2, ky, kx, za, zb, sa, sb) takes

@@ -34,18 +34,6 @@ namespace mf {
 
 namespace {
 
-// p / (p + T) to FP32 rounding: one Newton step on the reciprocal and one
-// correction with the exact remainder, the rounding of p + T included.
-__device__ __forceinline__ float wiener_f(float p, float T) {
-    const float den = p + T;
-    const float big = fmaxf(p, T), small = fminf(p, T);
-    const float lo = small - (den - big);  // p + T = den + lo exactly
-    float r = __builtin_amdgcn_rcpf(den);
-    r = fmaf(fmaf(-den, r, 1.0f), r, r);
-    const float q = p * r;
-    return fmaf(fmaf(-lo, q, fmaf(-den, q, p)), r, q);
-}
-
 // 1 - a and the source of one pixel: a d (Wiener filter) or T g (adjoint).
 __device__ __forceinline__ void pixel_coef(float nbar, float sv, float T, int32_t kind, float& oma, float& src) {
     const float aa = T * __builtin_amdgcn_rcpf(T + nbar);  // Nbar = inf: 0
@@ -117,9 +105,9 @@ __global__ __launch_bounds__(SolveShape<N>::type::NT, N == 128 ? 2 : 4) void res
             const unsigned ky = (e < RD ? dp.k1a : dp.k1b) + S::RC * (e % RD);
             const float2 w = a.tw[ky];  // (cos th, -sin th)
             const float* np = a.nP + pr.pix_off + (int64_t)ky * N + kx;
-            const float f0 = wiener_f(np[0], T), f1 = wiener_f(np[M * N], T);
-            fa[e] = fmaf(f0, 1.0f + w.y, f1 * (1.0f - w.y)) * scale;
-            fb[e] = (f0 - f1) * w.x * scale;
+            const RealFilter f = real_filter(np[0], np[M * N], T, w, scale);
+            fa[e] = f.a;
+            fb[e] = f.b;
         }
     };
 
