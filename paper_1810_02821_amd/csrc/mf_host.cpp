@@ -286,6 +286,25 @@ mf_status upload_spectrum(mf_plan p, int i, hipStream_t stream) {
     return MF_OK;
 }
 
+// Tables of problem i from its new band amplitudes (band edges unchanged, so
+// every mode keeps its band); the same values as upload_spectrum's.
+mf_status set_amplitudes(mf_plan p, int i, hipStream_t stream) {
+    const HostProblem& hp = p->probs[i];
+    const double n = (double)hp.H * hp.W;
+    mf::BandTables t{};
+    for (int b = 0; b < hp.n_bands; ++b) {
+        if (hp.band_modes[b] > 0 && !std::isfinite(n * hp.amps[b]))
+            return fail(MF_ERR_INVALID_ARG, "problem " + std::to_string(i) + ": P(k) must be finite and > 0 on every mode");
+        t.amp[b] = hp.amps[b];
+        t.scale[b] = 1.0 / (n * n * hp.amps[b] * hp.amps[b]);
+    }
+    MF_HIP(mf::launch_set_amplitudes(hp.W, hp.H, t, hp.n_bands, p->d_band + hp.pix_off, p->d_bandt + hp.pix_off,
+                                     p->d_nP + hp.pix_off, p->d_nPt + hp.pix_off / 2, p->d_band_amps + hp.band_base,
+                                     p->d_band_scale + hp.band_base, stream));
+    MF_HIP(hipStreamSynchronize(stream));
+    return MF_OK;
+}
+
 mf_status upload_twiddles(mf_plan p, int L) {
     if (p->d_tw.count(L)) return MF_OK;
     std::vector<float2> tw(L);
@@ -1874,7 +1893,14 @@ mf_status mf_plan_set_spectrum(mf_plan p, int32_t problem, const mf_spectrum* sp
     if (st != MF_OK) return st;
     if (tmp.kind != old_kind || tmp.n_bands != old_nb)
         return fail(MF_ERR_INVALID_ARG, "set_spectrum must keep the spectrum kind and band count");
+    // (a complete map: an upload that failed leaves one that covers fewer modes)
+    int64_t mapped = 0;
+    for (int32_t m : hp.band_modes) mapped += m;
+    const bool same_bands = hp.kind == MF_PK_BANDS && tmp.edges == hp.edges && mapped == (int64_t)hp.H * hp.W;
     hp = tmp;
+    // new amplitudes on the bands the plan already has (a training step): the
+    // tables are rewritten on the device from its band map
+    if (same_bands) return set_amplitudes(p, problem, (hipStream_t)stream);
     return upload_spectrum(p, problem, (hipStream_t)stream);
 }
 

@@ -181,6 +181,15 @@ hipError_t launch_loss_finish(const SweepArgs& a, const double* part, const doub
                               double* loss, double* grad_bands, hipStream_t s);
 // dof[b] = max(0, modes[b] + prior_dof) for b < n.
 hipError_t launch_band_dof(const int32_t* modes, int32_t prior_dof, int32_t* dof, int n, hipStream_t s);
+// n P(|k|) of a band problem from its band map and amplitudes: nP in mode order
+// (band), nPt in column pairs (bandt: the map column-major), and the amplitudes
+// and gradient scales of its bands.
+struct BandTables {
+    double amp[kMaxBandsPerProblem], scale[kMaxBandsPerProblem];
+};
+hipError_t launch_set_amplitudes(int W, int H, const BandTables& t, int n_bands, const int16_t* band,
+                                 const int16_t* bandt, float* nP, float2* nPt, double* amps, double* scale,
+                                 hipStream_t s);
 // y[i] += x[i] (float) for i < n.
 hipError_t launch_add(const float* x, float* y, int64_t n, hipStream_t s);
 

@@ -1059,6 +1059,27 @@ __global__ void scale_kernel(const float* x, const float* r, float* y, int64_t n
         y[e] = x[e] * r[e];
 }
 
+__global__ void set_amplitudes_kernel(BandTables t, int n_bands, int H, int W, const int16_t* band,
+                                      const int16_t* bandt, float* nP, float2* nPt, double* amps, double* scale) {
+    __shared__ float np[kMaxBandsPerProblem];  // n theta_b, evaluated in FP64
+    const double n = (double)H * (double)W;
+    for (int b = threadIdx.x; b < n_bands; b += blockDim.x) {
+        np[b] = (float)(n * t.amp[b]);
+        if (blockIdx.x == 0) {
+            amps[b] = t.amp[b];
+            scale[b] = t.scale[b];
+        }
+    }
+    __syncthreads();
+    const int half = H * W / 2;
+    for (int e = blockIdx.x * blockDim.x + threadIdx.x; e < half; e += gridDim.x * blockDim.x) {
+        nP[2 * e] = np[band[2 * e]];
+        nP[2 * e + 1] = np[band[2 * e + 1]];
+        const int p = e / H, ky = e % H;  // column pair, row
+        nPt[e] = make_float2(np[bandt[2 * p * H + ky]], np[bandt[(2 * p + 1) * H + ky]]);
+    }
+}
+
 // ------------------------------------------------------ sample moments --
 // Problem of a concatenated pixel index (problems are in pix_off order).
 __device__ __forceinline__ int problem_of(const ProbDev* probs, int n_problems, int64_t g) {
@@ -1633,6 +1654,14 @@ hipError_t launch_scale(const float* x, const float* r, float* y, int64_t n, hip
     return hipGetLastError();
 }
 
+hipError_t launch_set_amplitudes(int W, int H, const BandTables& t, int n_bands, const int16_t* band,
+                                 const int16_t* bandt, float* nP, float2* nPt, double* amps, double* scale,
+                                 hipStream_t s) {
+    const int half = H * W / 2;
+    hipLaunchKernelGGL(set_amplitudes_kernel, dim3((unsigned)std::min(1024, (half + 255) / 256)), dim3(256), 0, s, t,
+                       n_bands, H, W, band, bandt, nP, nPt, amps, scale);
+    return hipGetLastError();
+}
 hipError_t launch_grad_d(int W, int H, const SweepArgs& a, const float* v, float* grad_d, hipStream_t s) {
     hipLaunchKernelGGL(grad_d_kernel, elementwise_grid((int64_t)a.n_items * H * W), dim3(256), 0, s, a, H, W, v,
                        grad_d);

@@ -54,3 +54,38 @@ def test_the_residual_stops_where_the_oracle_stops(H, W):
     got = plan.split(s)[0]
     assert np.linalg.norm(got - ref) < 1e-5 * np.linalg.norm(ref)
     plan.close()
+
+
+@pytest.mark.parametrize("H,W,bands", [(24, 18, 2), (64, 128, 64), (256, 256, 32)])
+def test_new_amplitudes_on_the_same_bands_equal_a_new_plan(H, W, bands):
+    """mf_plan_set_spectrum rewrites the tables on the device when the band edges
+    stay; solves, gradients and the loss see the same values as a plan made with
+    the new spectrum, and as after a change of edges (the host path)."""
+    import types
+    import torch
+    import paper_1810_02821_amd as mf
+    from paper_1810_02821_amd import synth
+    prob = synth.config_bands(1, H, bands, W)
+    rng = np.random.default_rng(2)
+    amps = prob.spectrum.amps * rng.uniform(0.5, 2.0, bands)
+    new = types.SimpleNamespace(kind="bands", edges=prob.spectrum.edges, amps=amps)
+    wide = types.SimpleNamespace(kind="bands", edges=np.append(prob.spectrum.edges[:-1], 1e4), amps=amps)
+    fresh = synth.config_bands(1, H, bands, W)
+    fresh.spectrum = new
+    same, moved, made = mf.Plan([prob]), mf.Plan([prob]), mf.Plan([fresh])
+    same.set_spectrum(0, new)
+    moved.set_spectrum(0, wide)  # other edges, the same band for every mode
+    d, t = made.concat([prob.d]), made.concat([prob.s_true])
+    sch = mf.Schedule([10.0, 1.0], [3, 5])
+    out = []
+    for plan in (made, same, moved):
+        s, _ = plan.wiener(d, sch)
+        loss, gd, gb, _ = plan.band_loss(d, s, t, sch)
+        out.append((s, loss, gd, gb))
+        plan.close()
+    for got in out[1:]:
+        for a, b in zip(out[0], got):
+            if a.dtype == torch.float64:  # sums in an order that varies
+                assert float((a - b).abs().max()) <= 1e-12 * float(a.abs().max())
+            else:
+                assert torch.equal(a, b)
