@@ -104,7 +104,7 @@ struct mf_plan_s {
     int32_t* d_band_base = nullptr;
     int32_t* d_band_count = nullptr;
     double* d_band_scale = nullptr;  // 1 / (n^2 theta_b^2)
-    std::map<int, float2*> d_tw;     // W_L^r for every transform length L
+    std::map<int, float2*> d_tw;     // W_L^r for every transform length L, then the pairs of modulus 1 (unit_twiddle)
     // workspaces
     DevBuf items, field, t_save, partials, aux, coef;
     DevBuf field_adj, ckpt, tstore, slots;  // unrolled-gradient workspaces
@@ -305,17 +305,57 @@ mf_status set_amplitudes(mf_plan p, int i, hipStream_t stream) {
     return MF_OK;
 }
 
+// The FP32 pair near exp(i ang), 0 < ang < pi/2, whose modulus is closest to 1,
+// among pairs of up to four units in the last place from it (the distance from
+// the exact pair decides ties).  A solve multiplies by a twiddle in the forward
+// transform and by its conjugate in the inverse of the same sweep: the angle's
+// error cancels, the modulus' error (2^-25 for the nearest pair) is a gain that
+// every sweep repeats.
+float2 unit_twiddle(double ang) {
+    const double c = std::cos(ang), s = std::sin(ang);
+    float2 best = make_float2((float)c, (float)s);
+    float cs[9], ss[9];
+    cs[4] = best.x;
+    ss[4] = best.y;
+    for (int i = 1; i <= 4; ++i) {
+        cs[4 + i] = std::nextafter(cs[3 + i], 2.f);
+        cs[4 - i] = std::nextafter(cs[5 - i], -2.f);
+        ss[4 + i] = std::nextafter(ss[3 + i], 2.f);
+        ss[4 - i] = std::nextafter(ss[5 - i], -2.f);
+    }
+    double least = 1.0;
+    for (float x : cs)
+        for (float y : ss) {
+            const double e = std::fabs((double)x * x + (double)y * y - 1.0) + 0.02 * (std::fabs(x - c) + std::fabs(y - s));
+            if (e < least) {
+                least = e;
+                best = make_float2(x, y);
+            }
+        }
+    return best;
+}
+
 mf_status upload_twiddles(mf_plan p, int L) {
     if (p->d_tw.count(L)) return MF_OK;
-    std::vector<float2> tw(L);
+    // W_L^r, then the same with moduli of 1 (the transforms of the real-field
+    // solves, powers of two from 32; each octant from the first)
+    std::vector<float2> tw(2 * L), oct(L / 8 + 1);
+    const bool unit = is_pow2(L) && L >= 32;
+    for (int r = 1; unit && r <= L / 8; ++r) oct[r] = unit_twiddle(2.0 * M_PI * (double)r / (double)L);
     for (int r = 0; r < L; ++r) {
         const double ang = -2.0 * M_PI * (double)r / (double)L;
-        tw[r] = make_float2((float)std::cos(ang), (float)std::sin(ang));
+        tw[r] = tw[L + r] = make_float2((float)std::cos(ang), (float)std::sin(ang));
+        const int q = r % (L / 4);
+        if (!unit || q == 0) continue;
+        const float2 o = q <= L / 8 ? oct[q] : make_float2(oct[L / 4 - q].y, oct[L / 4 - q].x);
+        float2 w = make_float2(o.x, -o.y);
+        for (int k = 0; k < r / (L / 4); ++k) w = make_float2(w.y, -w.x);  // times -i
+        tw[L + r] = w;
     }
     float2* d = nullptr;
-    MF_HIP(hipMalloc(&d, L * sizeof(float2)));
+    MF_HIP(hipMalloc(&d, 2 * L * sizeof(float2)));
     p->d_tw[L] = d;
-    MF_HIP(hipMemcpy(d, tw.data(), L * sizeof(float2), hipMemcpyHostToDevice));
+    MF_HIP(hipMemcpy(d, tw.data(), 2 * L * sizeof(float2), hipMemcpyHostToDevice));
     return MF_OK;
 }
 
@@ -587,8 +627,9 @@ mf_status solve_class_real(mf_plan p, const std::vector<int>& pids, int H, int W
     a.src = src;
     a.nbar = p->d_nbar;
     a.nPt = p->d_nPt;
-    a.tw_w = p->d_tw.at(W);
-    a.tw_h = p->d_tw.at(H);
+    a.th = p->d_tw.at(W);
+    a.tw_w = p->d_tw.at(W) + W;
+    a.tw_h = p->d_tw.at(H) + H;
     a.s_init = s_init;
     a.s_out = out;
     a.t_save = p->t_save.as<float2>();
@@ -959,7 +1000,8 @@ mf_status solve_class_resident(mf_plan p, const std::vector<int>& pids, int N, c
     a.s_out = out;
     a.nbar = p->d_nbar;
     a.nP = p->d_nP;
-    a.tw = p->d_tw.at(N);
+    a.th = p->d_tw.at(N);
+    a.tw = p->d_tw.at(N) + N;
     a.max_sweeps = sch->max_sweeps;
     a.check_every = sch->check_every > 0 ? sch->check_every : 1;
     double* d_info = p->sched.as<double>();

@@ -60,7 +60,10 @@ __device__ __forceinline__ void sync_group() {
         __syncthreads();
     }
 }
-// One middle pass (as stockham_pass, with the synchronisation of the group).
+// A middle pass of radix R after NS points: forward as stockham_pass, from layout
+// AI to AO; inverse its adjoint, from AO back to AI (inverse butterfly, then the
+// conjugate twiddle).  With every pass of the inverse transform the adjoint of
+// one of the forward transform's, their twiddles' errors in angle cancel.
 template <int L, int R, int NS, int TPG, bool INV, int AI, int AO>
 __device__ __forceinline__ void real_pass(float2* buf, unsigned lane, const float2* tw) {
     constexpr bool WAVE = TPG <= 64;
@@ -70,15 +73,16 @@ __device__ __forceinline__ void real_pass(float2* buf, unsigned lane, const floa
     for (int t = 0; t < TPT; ++t) {
         const unsigned j = lane + t * TPG;
         if (NT % TPG == 0 || j < (unsigned)NT) {
+            const unsigned k = j % NS, o = (j / NS) * NS * R + k;
 #pragma unroll
-            for (int r = 0; r < R; ++r) v[t][r] = buf[lpos_step<AI, NT>(j, r)];
-            const unsigned k = j % NS;
+            for (int r = 0; r < R; ++r) v[t][r] = buf[INV ? lpos_write<AO, R, NS>(o, r) : lpos_step<AI, NT>(j, r)];
+            if constexpr (INV) dft<R, true>(v[t]);
 #pragma unroll
             for (int r = 1; r < R; ++r) {
                 const float2 w = tw[(r * k) * (L / (NS * R))];
                 v[t][r] = INV ? cmulc(v[t][r], w) : cmul(v[t][r], w);
             }
-            dft<R, INV>(v[t]);
+            if constexpr (!INV) dft<R, false>(v[t]);
         }
     }
     sync_group<WAVE>();
@@ -88,17 +92,45 @@ __device__ __forceinline__ void real_pass(float2* buf, unsigned lane, const floa
         if (NT % TPG == 0 || j < (unsigned)NT) {
             const unsigned o = (j / NS) * NS * R + j % NS;
 #pragma unroll
-            for (int r = 0; r < R; ++r) buf[lpos_write<AO, R, NS>(o, r)] = v[t][r];
+            for (int r = 0; r < R; ++r) buf[INV ? lpos_step<AI, NT>(j, r) : lpos_write<AO, R, NS>(o, r)] = v[t][r];
         }
     }
     sync_group<WAVE>();
 }
+// The transform of a row or column, element (mode) j + r L/4 at v[r] on both
+// sides; `buf` in LDS.
 template <int L, int TPG, bool INV>
-__device__ __forceinline__ void real_middle(float2* buf, unsigned lane, const float2* tw) {
+__device__ __forceinline__ void real_fft(float2 (&v)[4], float2* buf, unsigned j, const float2* tw) {
     using Y = RealLayout<L>;
-    real_pass<L, Y::M1, 4, TPG, INV, Y::A0, Y::A1>(buf, lane, tw);
-    real_pass<L, Y::M2, 4 * Y::M1, TPG, INV, Y::A1, Y::A2>(buf, lane, tw);
-    if constexpr (Y::M3 > 1) real_pass<L, Y::M3, 4 * Y::M1 * Y::M2, TPG, INV, Y::A2, Y::A3>(buf, lane, tw);
+    constexpr bool WAVE = TPG <= 64;
+    constexpr int Q = L / 4, N1 = 4, N2 = 4 * Y::M1, N3 = 4 * Y::M1 * Y::M2;
+    if constexpr (!INV) {
+        dft4<false>(v[0], v[1], v[2], v[3]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) buf[lpos_run<Y::A0, 4>(j, r)] = v[r];
+        sync_group<WAVE>();
+        real_pass<L, Y::M1, N1, TPG, false, Y::A0, Y::A1>(buf, j, tw);
+        real_pass<L, Y::M2, N2, TPG, false, Y::A1, Y::A2>(buf, j, tw);
+        if constexpr (Y::M3 > 1) real_pass<L, Y::M3, N3, TPG, false, Y::A2, Y::A3>(buf, j, tw);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = buf[lpos_step<Y::AL, Q>(j, r)];
+#pragma unroll
+        for (int r = 1; r < 4; ++r) v[r] = cmul(v[r], tw[r * j]);
+        dft4<false>(v[0], v[1], v[2], v[3]);
+    } else {
+        dft4<true>(v[0], v[1], v[2], v[3]);
+#pragma unroll
+        for (int r = 1; r < 4; ++r) v[r] = cmulc(v[r], tw[r * j]);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) buf[lpos_step<Y::AL, Q>(j, r)] = v[r];
+        sync_group<WAVE>();
+        if constexpr (Y::M3 > 1) real_pass<L, Y::M3, N3, TPG, true, Y::A2, Y::A3>(buf, j, tw);
+        real_pass<L, Y::M2, N2, TPG, true, Y::A1, Y::A2>(buf, j, tw);
+        real_pass<L, Y::M1, N1, TPG, true, Y::A0, Y::A1>(buf, j, tw);
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = buf[lpos_run<Y::A0, 4>(j, r)];
+        dft4<true>(v[0], v[1], v[2], v[3]);
+    }
 }
 
 // Offset of row y (column c) of a field in 4 x 4 tiles of M columns; element
@@ -150,17 +182,9 @@ __global__ __launch_bounds__(RealRow<L>::NTH) void real_row_kernel(RealArgs a) {
     }
 #pragma unroll
     for (int i = 0; i < L / NTH; ++i) twl[tid + i * NTH] = tw[2 * (tid + i * NTH)];
+    __syncthreads();  // the twiddles
     if constexpr (MODE & kRowInv) {
-        dft4<true>(v[0], v[1], v[2], v[3]);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) row[lpos_run<Y::A0, 4>(lane, r)] = v[r];
-        __syncthreads();  // and the twiddles
-        real_middle<L, Q, true>(row, lane, twl);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = row[lpos_step<Y::AL, Q>(lane, r)];
-#pragma unroll
-        for (int r = 1; r < 4; ++r) v[r] = cmulc(v[r], twl[r * lane]);
-        dft4<true>(v[0], v[1], v[2], v[3]);
+        real_fft<L, Q, true>(v, row, lane, twl);
         // v[r] is the state at pixels 2x, 2x + 1, x = lane + r L/4
         if constexpr (!(MODE & kRowFwd)) {
             float* o = a.s_out + prow + 2 * lane;
@@ -216,18 +240,8 @@ __global__ __launch_bounds__(RealRow<L>::NTH) void real_row_kernel(RealArgs a) {
                 for (int r = 0; r < 4; ++r) ts[4 * Q * r] = v[r];
             }
         }
-        dft4<false>(v[0], v[1], v[2], v[3]);
-        sync_group<WAVE>();
-#pragma unroll
-        for (int r = 0; r < 4; ++r) row[lpos_run<Y::A0, 4>(lane, r)] = v[r];
-        if constexpr (MODE & kRowInv) sync_group<WAVE>();
-        else __syncthreads();  // and the twiddles
-        real_middle<L, Q, false>(row, lane, twl);
-#pragma unroll
-        for (int r = 0; r < 4; ++r) v[r] = row[lpos_step<Y::AL, Q>(lane, r)];
-#pragma unroll
-        for (int r = 1; r < 4; ++r) v[r] = cmul(v[r], twl[r * lane]);
-        dft4<false>(v[0], v[1], v[2], v[3]);
+        sync_group<WAVE>();  // the row's last reads are done
+        real_fft<L, Q, false>(v, row, lane, twl);
 #pragma unroll
         for (int r = 0; r < 4; ++r) fld[4 * Q * r] = v[r];
     }
@@ -265,21 +279,13 @@ __global__ __launch_bounds__(L / 2) void real_col_kernel(RealArgs a) {
         q0[r] = np[r * Q];
         q1[r] = np[r * Q + (int64_t)(M >> 1) * L];
     }
-    const float2 th = a.tw_w[c];  // (cos th, -sin th)
+    const float2 th = a.th[c];  // (cos th, -sin th)
 #pragma unroll
     for (int i = 0; i < (L + NTH - 1) / NTH; ++i)
         if (L % NTH == 0 || tid + i * NTH < (unsigned)L) twl[tid + i * NTH] = a.tw_h[tid + i * NTH];
     float2* col = lds + slot * SEG;
-    dft4<false>(v[0], v[1], v[2], v[3]);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) col[lpos_run<Y::A0, 4>(j, r)] = v[r];
-    __syncthreads();  // and the twiddles
-    real_middle<L, Q, false>(col, j, twl);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) v[r] = col[lpos_step<Y::AL, Q>(j, r)];
-#pragma unroll
-    for (int r = 1; r < 4; ++r) v[r] = cmul(v[r], twl[r * j]);
-    dft4<false>(v[0], v[1], v[2], v[3]);
+    __syncthreads();  // the twiddles
+    real_fft<L, Q, false>(v, col, j, twl);
     sync_group<WAVE>();
 #pragma unroll
     for (int r = 0; r < 4; ++r) col[lpos_step<AN, Q>(j, r)] = v[r];
@@ -300,17 +306,8 @@ __global__ __launch_bounds__(L / 2) void real_col_kernel(RealArgs a) {
             v[r] = make_float2(fmaf(f.a, v[r].x, f.b * zm.y), fmaf(f.a, v[r].y, f.b * zm.x));
         }
     }
-    dft4<true>(v[0], v[1], v[2], v[3]);
-    __syncthreads();
-#pragma unroll
-    for (int r = 0; r < 4; ++r) col[lpos_run<Y::A0, 4>(j, r)] = v[r];
-    sync_group<WAVE>();
-    real_middle<L, Q, true>(col, j, twl);
-#pragma unroll
-    for (int r = 0; r < 4; ++r) v[r] = col[lpos_step<Y::AL, Q>(j, r)];
-#pragma unroll
-    for (int r = 1; r < 4; ++r) v[r] = cmulc(v[r], twl[r * j]);
-    dft4<true>(v[0], v[1], v[2], v[3]);
+    __syncthreads();  // the other column has read its mirrors
+    real_fft<L, Q, true>(v, col, j, twl);
 #pragma unroll
     for (int r = 0; r < 4; ++r) fld[Q * M * r] = v[r];
 }

@@ -21,8 +21,9 @@ struct RealArgs {
     const float* src;         // concatenated data d or adjoint rhs g
     const float* nbar;        // concatenated Nbar (+inf missing)
     const float2* nPt;        // column-pair table of n P(|k|): [pix_off/2 + (kx/2) H + ky] = (kx, kx + 1)
-    const float2* tw_w;       // W_W^r, r < W
-    const float2* tw_h;       // W_H^r, r < H
+    const float2* th;         // W_W^r, r < W, to the nearest (the fold's angles)
+    const float2* tw_w;       // W_W^r and W_H^r of modulus 1 (the transforms' twiddles)
+    const float2* tw_h;
     const float* s_init;      // kRowFwd: concatenated start, or null for zero
     float* s_out;             // kRowInv: concatenated result
     float2* t_save;           // messenger snapshot (field layout), or null

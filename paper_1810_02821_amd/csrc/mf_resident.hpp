@@ -38,7 +38,8 @@ struct SolveArgs {
     float* s_out;             // concatenated result
     const float* nbar;        // concatenated Nbar (+inf missing)
     const float* nP;          // concatenated n P(|k|)
-    const float2* tw;         // W_N^r, r < N
+    const float2* th;         // W_N^r, r < N, to the nearest (the fold's angles)
+    const float2* tw;         // W_N^r of modulus 1 (the transforms' twiddles)
     Levels lv;                // cooling levels of this launch
     int32_t total0;           // sweeps run by earlier launches of the same solve
     double tol;               // residual tolerance of the final level (<= 0: none; only in the last launch)

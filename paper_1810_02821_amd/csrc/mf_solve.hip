@@ -103,7 +103,7 @@ __global__ __launch_bounds__(SolveShape<N>::type::NT, N == 128 ? 2 : 4) void res
         for (int e = 0; e < V; ++e) {
             const unsigned kx = e < RD ? dp.kxa : dp.kxb;
             const unsigned ky = (e < RD ? dp.k1a : dp.k1b) + S::RC * (e % RD);
-            const float2 w = a.tw[ky];  // (cos th, -sin th)
+            const float2 w = a.th[ky];  // (cos th, -sin th)
             const float* np = a.nP + pr.pix_off + (int64_t)ky * N + kx;
             const RealFilter f = real_filter(np[0], np[M * N], T, w, scale);
             fa[e] = f.a;
