@@ -5,6 +5,8 @@
 #include <hip/hip_runtime.h>
 #include <stdint.h>
 
+#include "mf_pass_plan.hpp"
+
 namespace mf {
 
 // ---------------------------------------------------------------- complex --
@@ -195,16 +197,34 @@ constexpr int pad_of(int L, int R, int NS) {
 // including the position of element L - 1).
 constexpr int pad_len(int L, int A) { return A < 0 ? L : L + A * ((L - 1) / 32); }
 
+// Pass tables of which those with NS <= LIM are in LDS.
+template <int LIM>
+struct TwSplit {
+    const float2* g;
+    const float2* l;
+};
+template <int L, int R, int NS>
+__device__ __forceinline__ const float2* pass_table(const float2* tw) {
+    constexpr int off = pass_tw(L, R, NS);
+    static_assert(off >= 0, "a pass of the plan of L");
+    return tw + off;
+}
+template <int L, int R, int NS, int LIM>
+__device__ __forceinline__ const float2* pass_table(const TwSplit<LIM>& tw) {
+    if constexpr (NS <= LIM) return pass_table<L, R, NS>(tw.l);
+    else return pass_table<L, R, NS>(tw.g);
+}
+
 // One radix-R pass of a length-L transform held in `buf`, reading the
 // exchange in layout AI and writing in layout AO.  `lane` in [0, TPG)
 // indexes the TPG threads that own this transform; NS is the product of the
 // radices already applied.  Input in the Stockham order of the previous pass,
 // output in the order of the next; after the last pass the sequence is in
-// natural order.  `tw` holds W_L^r, r < L.  The pass reads every element into
+// natural order.  `tw` holds the pass tables of L (pass_plan).  The pass reads every element into
 // registers before writing (in place), so it needs the two barriers; every
 // thread of the block must call it.
-template <int L, int R, int NS, int TPG, bool INV, int AI = -1, int AO = -1>
-__device__ __forceinline__ void stockham_pass(float2* buf, unsigned lane, const float2* __restrict__ tw) {
+template <int L, int R, int NS, int TPG, bool INV, int AI = -1, int AO = -1, typename TW>
+__device__ __forceinline__ void stockham_pass(float2* buf, unsigned lane, const TW& tw) {
     constexpr int NT = L / R;
     constexpr int TPT = (NT + TPG - 1) / TPG;
     float2 v[TPT][R];
@@ -215,10 +235,10 @@ __device__ __forceinline__ void stockham_pass(float2* buf, unsigned lane, const 
 #pragma unroll
             for (int r = 0; r < R; ++r) v[t][r] = buf[lpos_step<AI, NT>(j, r)];
             if constexpr (NS > 1) {
-                const unsigned k = j % NS;
+                const float2* wk = pass_table<L, R, NS>(tw) + j % NS;
 #pragma unroll
                 for (int r = 1; r < R; ++r) {
-                    const float2 w = tw[(r * k) * (L / (NS * R))];
+                    const float2 w = wk[(r - 1) * NS];
                     v[t][r] = INV ? cmulc(v[t][r], w) : cmul(v[t][r], w);
                 }
             }
@@ -239,20 +259,11 @@ __device__ __forceinline__ void stockham_pass(float2* buf, unsigned lane, const 
     __syncthreads();
 }
 
-// Transform lengths: 2^a 3^b with a >= 1 (even sides).
-constexpr bool is_pow2(int L) { return L > 0 && (L & (L - 1)) == 0; }
-
-// Radix plan: radix-16 passes while 16 divides what is left, then one
-// radix-8/4/2 pass for the rest of the power of two, then radix-3 passes.
-template <int REM>
-constexpr int next_radix() {
-    return REM % 16 == 0 ? 16 : REM % 8 == 0 ? 8 : REM % 4 == 0 ? 4 : REM % 2 == 0 ? 2 : 3;
-}
 // A whole transform in LDS, reading layout AI and leaving its natural-order
 // output in layout AOUT; with AI >= 0 the exchanges between its passes take
 // the pads pad_of picks, otherwise the XOR swizzle.
-template <int L, int NS, int TPG, bool INV, int AI = -1, int AOUT = -1>
-__device__ __forceinline__ void stockham_fft(float2* buf, unsigned lane, const float2* __restrict__ tw) {
+template <int L, int NS, int TPG, bool INV, int AI = -1, int AOUT = -1, typename TW>
+__device__ __forceinline__ void stockham_fft(float2* buf, unsigned lane, const TW& tw) {
     if constexpr (NS < L) {
         constexpr int R = next_radix<L / NS>();
         static_assert((L / NS) % R == 0, "transform length must be 2^a 3^b");

@@ -15,6 +15,7 @@
 
 #include "../../include/mf.h"
 #include "mf_kernels.hpp"
+#include "mf_pass_plan.hpp"
 #include "mf_resident.hpp"
 #include "mf_real.hpp"
 #include "mf_spectrum.hpp"
@@ -104,7 +105,7 @@ struct mf_plan_s {
     int32_t* d_band_base = nullptr;
     int32_t* d_band_count = nullptr;
     double* d_band_scale = nullptr;  // 1 / (n^2 theta_b^2)
-    std::map<int, float2*> d_tw;     // W_L^r for every transform length L, then the pairs of modulus 1 (unit_twiddle)
+    std::map<int, float2*> d_tw;     // W_L^r for every transform length L, the pairs of modulus 1 (unit_twiddle), the pass tables (pass_plan)
     // workspaces
     DevBuf items, field, t_save, partials, aux, coef;
     DevBuf field_adj, ckpt, tstore, slots;  // unrolled-gradient workspaces
@@ -352,10 +353,17 @@ mf_status upload_twiddles(mf_plan p, int L) {
         for (int k = 0; k < r / (L / 4); ++k) w = make_float2(w.y, -w.x);  // times -i
         tw[L + r] = w;
     }
+    // then the pass tables of the streamed transforms
+    const mf::PassPlan plan = mf::pass_plan(L);
+    tw.resize(2 * L + plan.size);
+    for (int i = 0; i < plan.n; ++i)
+        for (int r = 1; r < plan.R[i]; ++r)
+            for (int k = 0; k < plan.NS[i]; ++k)
+                tw[2 * L + plan.off[i] + (r - 1) * plan.NS[i] + k] = tw[r * k * (L / (plan.R[i] * plan.NS[i]))];
     float2* d = nullptr;
-    MF_HIP(hipMalloc(&d, 2 * L * sizeof(float2)));
+    MF_HIP(hipMalloc(&d, tw.size() * sizeof(float2)));
     p->d_tw[L] = d;
-    MF_HIP(hipMemcpy(d, tw.data(), 2 * L * sizeof(float2), hipMemcpyHostToDevice));
+    MF_HIP(hipMemcpy(d, tw.data(), tw.size() * sizeof(float2), hipMemcpyHostToDevice));
     return MF_OK;
 }
 
@@ -382,21 +390,21 @@ std::pair<int, int> class_shape(mf_plan p, int H, int W) {
 
 // The tile of a launch over n_items work items: the class's shape, or its
 // narrow shape when the class's shape would leave CUs idle.  A default tile
-// that reads its twiddles from L2 relies on a second workgroup per CU to hide
-// them; a launch giving each CU at most two such tiles has none to overlap and
-// takes the widest candidate with LDS twiddles that still gives every CU a
+// chosen because two fit in a CU overlaps one's memory phases with the other's
+// arithmetic; a launch giving each CU at most two such tiles has little to
+// overlap and takes the widest other candidate that still gives every CU a
 // workgroup (one 2048^2 field: 8 x 512 instead of 4 x 256).
 std::pair<int, int> class_shape(mf_plan p, int H, int W, int64_t n_items) {
     const auto wide = class_shape(p, H, W);
     const int64_t tiles = n_items * ((W + wide.first - 1) / wide.first);
     if (tiles >= mf::kFillBlocks) {
-        if (tiles <= 2 * mf::kFillBlocks && mf::col_tw_in_l2(H, wide.first) &&
+        if (tiles <= 2 * mf::kFillBlocks && mf::col_tile_twice(H, wide.first) &&
             p->col_shape.find({H, W}) == p->col_shape.end()) {
             int tc[8], nth[8];
             const int k = mf::col_shape_candidates(H, tc, nth, 8);
             int b = -1;
             for (int i = 0; i < k; ++i)
-                if (!mf::col_tw_in_l2(H, tc[i]) && n_items * ((W + tc[i] - 1) / tc[i]) >= mf::kFillBlocks &&
+                if (!mf::col_tile_twice(H, tc[i]) && n_items * ((W + tc[i] - 1) / tc[i]) >= mf::kFillBlocks &&
                     (b < 0 || tc[i] > tc[b]))
                     b = i;
             if (b >= 0) return {tc[b], nth[b]};
@@ -421,8 +429,8 @@ mf::SweepArgs base_args(mf_plan p, int H, int W) {
     a.nbar = p->d_nbar;
     a.nP = p->d_nP;
     a.nPt = p->d_nPt;
-    a.tw_row = p->d_tw.at(W);
-    a.tw_col = p->d_tw.at(H);
+    a.tw_row = p->d_tw.at(W) + 2 * W;
+    a.tw_col = p->d_tw.at(H) + 2 * H;
     a.lambda = 1.0f;
     a.emit_index = -1;
     auto rr = p->row_rows.find({H, W});
@@ -838,8 +846,8 @@ mf_status shear_streamed(mf_plan p, const mf::ItemDev* di, int n_items, int H, i
     a.nP = p->d_nP;
     a.nPt = p->d_nPt;
     a.b_ratio = b_ratio;
-    a.tw_row = p->d_tw.at(W);
-    a.tw_col = p->d_tw.at(H);
+    a.tw_row = p->d_tw.at(W) + 2 * W;
+    a.tw_col = p->d_tw.at(H) + 2 * H;
     a.key0 = (uint32_t)(seed & 0xffffffffu);
     a.key1 = (uint32_t)(seed >> 32);
     a.stochastic = stochastic;
@@ -1203,7 +1211,7 @@ mf_status spectrum_streamed(mf_plan p, const mf::ItemDev* di, int n_items, int H
     r.items = di;
     r.n_items = n_items;
     r.field = work;
-    r.tw_col = p->d_tw.at(H);
+    r.tw_col = p->d_tw.at(H) + 2 * H;
     r.band = p->d_band;
     r.bandt = p->d_bandt;
     r.band_base = p->d_band_base;

@@ -52,8 +52,8 @@ struct SweepArgs {
     const float* nbar;        // concatenated Nbar (+inf missing)
     const float* nP;          // concatenated n P(|k|) per mode (unshifted order)
     const float2* nPt;        // column-pair table: [pix_off/2 + (kx/2) H + ky] = (nP(ky,kx), nP(ky,kx+1)), or null
-    const float2* tw_row;     // twiddles W_W^r
-    const float2* tw_col;     // twiddles W_H^r
+    const float2* tw_row;     // pass tables of W (pass_plan)
+    const float2* tw_col;     // pass tables of H
     float lambda;             // cooling level: T = lambda * tau
     int32_t stochastic;       // 1: draw variates (sampler), 0: Wiener iteration
     uint32_t key0, key1;      // Philox key
@@ -112,10 +112,9 @@ int fused_row_candidates(int W, int* rows, int max_n);
 // than the GPU has CUs (a single solve, a few chains) takes the narrow shape
 // instead: tuned on one item, else the candidate with the most blocks.
 constexpr int kFillBlocks = 256;
-// Column tiles that read their twiddles from L2 instead of LDS: 4 columns of
-// 2048 rows, so that two workgroups fit in a CU's LDS and one's memory phases
-// overlap the other's.
-constexpr bool col_tw_in_l2(int L, int tc) { return L == 2048 && tc <= 4; }
+// Column tiles of which two workgroups fit in a CU's LDS although the length's
+// wider tiles fit only once: 4 columns of 2048 rows.
+constexpr bool col_tile_twice(int L, int tc) { return L == 2048 && tc <= 4; }
 void narrow_col_shape(int H, int* tc, int* nth);
 int narrow_row_rows(int W);
 // Sum per-tile band slots into out[band_base[prob] + b] for every item.

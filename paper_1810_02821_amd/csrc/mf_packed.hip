@@ -60,7 +60,7 @@ __global__ __launch_bounds__(PackShape<L>::NTH) void col_pack_kernel(SweepArgs a
     constexpr int TC = PackShape<L>::TC, NTH = PackShape<L>::NTH, TPC = PackShape<L>::TPC;
     // padded exchange layouts from 256 rows (the HBM-side passes) where they
     // keep the resident workgroups per CU, else the XOR swizzle
-    constexpr int kExtra = 8 * L;  // twiddles and tables beside the tile
+    constexpr int kExtra = 8 * lds_tw_len<L>();  // the twiddles beside the tile
     constexpr bool kPad = L >= 256 && lds_keeps_blocks(TC * PackShape<L>::SEG * 8 + kExtra,
                                                        TC * PairLayout<L, TC>::SEG * 8 + kExtra);
     constexpr int A1 = kPad ? PairLayout<L, TC>::A1 : -1, AN = kPad ? PairLayout<L, TC>::AN : -1;
@@ -69,7 +69,8 @@ __global__ __launch_bounds__(PackShape<L>::NTH) void col_pack_kernel(SweepArgs a
     constexpr int H = L;
     constexpr int half = TC / 2;
     __shared__ float2 lds[TC * SEG];
-    __shared__ float2 twl[L >= 256 ? L : 1];
+    __shared__ float2 twl[L >= 256 ? lds_tw_len<L>() : 1];
+    const TwSplit<lds_tw_lim(L)> tws{a.tw_col, twl};
     const unsigned tid = threadIdx.x;
     const int64_t t = xcd_block(blockIdx.x, gridDim.x);
     const int item = (int)(t / (W / TC));
@@ -82,7 +83,7 @@ __global__ __launch_bounds__(PackShape<L>::NTH) void col_pack_kernel(SweepArgs a
     auto col_of = [&](int s) { return mirror_column(j, s, half, W); };
     if constexpr (L >= 256) {
         col_first_forward<L, TC, NTH, SEG, A1>(lds, fld, W, tid, col_of);
-        for (unsigned i = tid; i < (unsigned)L; i += NTH) twl[i] = a.tw_col[i];
+        stage_twiddles<L, NTH>(twl, a.tw_col, tid);
     } else {
         for (unsigned e = tid; e < (unsigned)(TC * L); e += NTH) {
             const int s = (int)(e % TC), y = (int)(e / TC);
@@ -91,7 +92,7 @@ __global__ __launch_bounds__(PackShape<L>::NTH) void col_pack_kernel(SweepArgs a
     }
     __syncthreads();
     const unsigned cid = tid / TPC, lane = tid % TPC;
-    if constexpr (L >= 256) col_forward_rest<L, TPC, A1>(lds + cid * SEG, lane, twl);
+    if constexpr (L >= 256) col_forward_rest<L, TPC, A1>(lds + cid * SEG, lane, tws);
     else stockham_fft<L, 1, TPC, false>(lds + cid * SEG, lane, a.tw_col);
 
     const float TA = a.lambda * pa.tau, TB = a.lambda * pb.tau;
@@ -203,8 +204,8 @@ __global__ __launch_bounds__(PackShape<L>::NTH) void col_pack_kernel(SweepArgs a
     }
     __syncthreads();
     if constexpr (L >= 256) {
-        col_inverse_head<L, TPC, AN>(lds + opaque_u(cid) * SEG, opaque_u(lane), twl + opaque_u(0u));
-        col_last_inverse<L, TC, NTH, SEG, AD>(lds, fld, W, opaque_u(tid), twl + opaque_u(0u), col_of);
+        col_inverse_head<L, TPC, AN>(lds + opaque_u(cid) * SEG, opaque_u(lane), opaque(tws));
+        col_last_inverse<L, TC, NTH, SEG, AD>(lds, fld, W, opaque_u(tid), opaque(tws), col_of);
     } else {
         stockham_fft<L, 1, TPC, true>(lds + opaque_u(cid) * SEG, opaque_u(lane), a.tw_col);
         for (unsigned e = tid; e < (unsigned)(TC * L); e += NTH) {

@@ -48,8 +48,8 @@ struct ShearStreamArgs {
     const float* nP;          // concatenated n P_E(|k|)
     const float2* nPt;        // column-pair copy: [pix_off/2 + (kx/2) H + ky] = (nP(ky,kx), nP(ky,kx+1))
     float b_ratio;
-    const float2* tw_row;     // W_W^r
-    const float2* tw_col;     // W_H^r
+    const float2* tw_row;     // pass tables of W (pass_plan)
+    const float2* tw_col;     // pass tables of H (pass_plan)
     uint32_t key0, key1;
     uint32_t sweep;           // global sweep index
     float lambda;             // cooling level: T = lambda * tau

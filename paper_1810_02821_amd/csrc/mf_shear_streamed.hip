@@ -209,6 +209,7 @@ __global__ __launch_bounds__(kRowThreads) void shear_row_kernel_f(ShearStreamArg
                                                                                  : pad_max(L, RM, RL, 16, AF);
     constexpr int LP = pad_len(L, AMAX);  // row stride in LDS
     __shared__ float2 lds[ROWS * LP];
+    __shared__ float2 twl[lds_tw_len<L>()];
     __shared__ int32_t row_item[ROWS], row_y[ROWS];
     const unsigned tid = threadIdx.x;
     const int64_t total_rows = (int64_t)a.n_items * H;
@@ -218,6 +219,7 @@ __global__ __launch_bounds__(kRowThreads) void shear_row_kernel_f(ShearStreamArg
         row_item[r] = g < total_rows ? (int32_t)(g % a.n_items) : -1;
         row_y[r] = g < total_rows ? (int32_t)(g / a.n_items) : 0;
     }
+    const auto twr = stage_twiddles<L, kRowThreads>(twl, a.tw_row, tid);
     __syncthreads();
     const unsigned rid = tid / TPR, lane = tid % TPR;
     const bool valid = row_item[rid] >= 0;
@@ -243,7 +245,7 @@ __global__ __launch_bounds__(kRowThreads) void shear_row_kernel_f(ShearStreamArg
         }
     }
     __syncthreads();
-    passes_before<L, RM, 16, RL, TPR, true, A1>(row, lane, a.tw_row);
+    passes_before<L, RM, 16, RL, TPR, true, A1>(row, lane, twr);
 
     // last inverse pass, pixel step t = (1 - a) s + a gamma (+ sqrt(T (1 - a)) xi),
     // first forward pass
@@ -257,7 +259,7 @@ __global__ __launch_bounds__(kRowThreads) void shear_row_kernel_f(ShearStreamArg
 #pragma unroll
             for (int r = 0; r < RL; ++r) v[i][r] = row[lpos_step<AC, NTL>(j, r)];
 #pragma unroll
-            for (int r = 1; r < RL; ++r) v[i][r] = cmulc(v[i][r], a.tw_row[r * j]);
+            for (int r = 1; r < RL; ++r) v[i][r] = cmulc(v[i][r], last_tw<L, RL>(twr, r, j));
             dft<RL, true>(v[i]);
             float2 z[RL];
 #pragma unroll
@@ -307,10 +309,10 @@ __global__ __launch_bounds__(kRowThreads) void shear_row_kernel_f(ShearStreamArg
     }
 
     // middle forward passes, then the last one (NS = L/16) to HBM
-    passes_before<L, RM, RL, 16, TPR, false, AF>(row, opaque(lane), opaque(a.tw_row));
+    passes_before<L, RM, RL, 16, TPR, false, AF>(row, opaque(lane), opaque(twr));
     if (valid) {
         const unsigned lane2 = opaque(lane);
-        const float2* tw = opaque(a.tw_row);
+        const auto tw = opaque(twr);
 #pragma unroll
         for (int i = 0; i < IT16; ++i) {
             const unsigned j = lane2 + i * TPR;
@@ -319,7 +321,7 @@ __global__ __launch_bounds__(kRowThreads) void shear_row_kernel_f(ShearStreamArg
 #pragma unroll
                 for (int r = 0; r < 16; ++r) v[r] = row[lpos_step<AD, NT16>(j, r)];
 #pragma unroll
-                for (int r = 1; r < 16; ++r) v[r] = cmul(v[r], tw[r * j]);
+                for (int r = 1; r < 16; ++r) v[r] = cmul(v[r], last_tw<L, 16>(tw, r, j));
                 dft<16, false>(v);
 #pragma unroll
                 for (int r = 0; r < 16; ++r) frow[j + r * NT16] = v[r];
@@ -334,7 +336,7 @@ __global__ __launch_bounds__(ShearColShape<L>::NTH) void shear_col_kernel(ShearS
     // padded exchange layouts from 256 rows (the HBM-side passes) where they
     // keep the resident workgroups per CU, else the XOR swizzle; an emission
     // sweep's round trip starts and ends in the natural-order layout AN
-    constexpr int kExtra = 8 * L;  // the twiddle table beside the tile
+    constexpr int kExtra = 8 * lds_tw_len<L>();  // the twiddles beside the tile
     constexpr bool kPad = L >= 256 && lds_keeps_blocks(TC * ShearColShape<L>::SEG * 8 + kExtra,
                                                        TC * PairLayout<L, TC>::SEG * 8 + kExtra);
     constexpr int A1 = kPad ? PairLayout<L, TC>::A1 : -1, AN = kPad ? PairLayout<L, TC>::AN : -1;
@@ -343,7 +345,8 @@ __global__ __launch_bounds__(ShearColShape<L>::NTH) void shear_col_kernel(ShearS
     constexpr int H = L;
     constexpr int half = TC / 2;
     __shared__ float2 lds[TC * SEG];
-    __shared__ float2 twl[L >= 256 ? L : 1];  // twiddles of the HBM-side passes
+    __shared__ float2 twl[L >= 256 ? lds_tw_len<L>() : 1];  // twiddles of the HBM-side passes
+    const TwSplit<lds_tw_lim(L)> tws{a.tw_col, twl};
     const unsigned tid = threadIdx.x;
     // tile fastest: an XCD runs neighbouring tiles of one item together
     const int64_t t = xcd_block(blockIdx.x, gridDim.x);
@@ -357,10 +360,10 @@ __global__ __launch_bounds__(ShearColShape<L>::NTH) void shear_col_kernel(ShearS
     const unsigned cid = tid / TPC, lane = tid % TPC;
     if constexpr (L >= 256) {
         // first forward pass straight from HBM (plan of mf_streamed_fft.hpp)
-        for (unsigned i = tid; i < (unsigned)L; i += NTH) twl[i] = a.tw_col[i];
+        stage_twiddles<L, NTH>(twl, a.tw_col, tid);
         col_first_forward<L, TC, NTH, SEG, A1>(lds, fin, W, tid, col_of);
         __syncthreads();
-        col_forward_rest<L, TPC, A1>(lds + cid * SEG, lane, twl);
+        col_forward_rest<L, TPC, A1>(lds + cid * SEG, lane, tws);
     } else {
         for (unsigned e = tid; e < (unsigned)(TC * L); e += NTH) {
             const int s = (int)(e % TC), y = (int)(e / TC);
@@ -481,8 +484,8 @@ __global__ __launch_bounds__(ShearColShape<L>::NTH) void shear_col_kernel(ShearS
     float2* fout = a.field + it.field_off;
     if constexpr (L >= 256) {
         // inverse transform, its last pass straight to HBM
-        col_inverse_head<L, TPC, AN>(lds + opaque(cid) * SEG, opaque(lane), twl + opaque(0u));
-        col_last_inverse<L, TC, NTH, SEG, AD>(lds, fout, W, opaque(tid), twl + opaque(0u), col_of);
+        col_inverse_head<L, TPC, AN>(lds + opaque(cid) * SEG, opaque(lane), opaque(tws));
+        col_last_inverse<L, TC, NTH, SEG, AD>(lds, fout, W, opaque(tid), opaque(tws), col_of);
     } else {
         stockham_fft<L, 1, TPC, true>(lds + opaque(cid) * SEG, opaque(lane), opaque(a.tw_col));
         for (unsigned e = tid; e < (unsigned)(TC * L); e += NTH) {

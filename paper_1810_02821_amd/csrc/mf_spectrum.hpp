@@ -48,7 +48,7 @@ struct SpectrumStreamArgs {
     const ItemDev* items;
     int32_t n_items;
     float2* field;            // pair fields, items' layout
-    const float2* tw_col;     // W_H^r
+    const float2* tw_col;     // pass tables of H (pass_plan)
     const int16_t* band;      // per-mode band index (concatenated)
     const int16_t* bandt;     // the same, column-major per problem: [pix_off + kx H + ky]
     const int32_t* band_base;

@@ -70,7 +70,7 @@ __global__ __launch_bounds__(PairShape<L>::NTH) void col_pair_kernel(SpectrumStr
     constexpr int TC = PairShape<L>::TC, NTH = PairShape<L>::NTH, TPC = PairShape<L>::TPC;
     // padded exchange layouts from 256 rows (the HBM-side passes) where they
     // keep the resident workgroups per CU, else the XOR swizzle
-    constexpr int kExtra = 8 * L + (int)(sizeof(double) * 2 * kNB + sizeof(float4) * kNB);  // twiddles and tables beside the tile
+    constexpr int kExtra = 8 * lds_tw_len<L>() + (int)(sizeof(double) * 2 * kNB + sizeof(float4) * kNB);  // twiddles and tables beside the tile
     constexpr bool kPad = L >= 256 && lds_keeps_blocks(TC * PairShape<L>::SEG * 8 + kExtra,
                                                        TC * PairLayout<L, TC>::SEG * 8 + kExtra);
     constexpr int A1 = kPad ? PairLayout<L, TC>::A1 : -1, AN = kPad ? PairLayout<L, TC>::AN : -1;
@@ -81,7 +81,8 @@ __global__ __launch_bounds__(PairShape<L>::NTH) void col_pair_kernel(SpectrumStr
     __shared__ float2 lds[TC * SEG];
     __shared__ double pw[2][kNB];
     __shared__ float4 coef[kNB];
-    __shared__ float2 twl[L >= 256 ? L : 1];  // twiddles in LDS (hierarchical 2048^2 sweep +7%)
+    __shared__ float2 twl[L >= 256 ? lds_tw_len<L>() : 1];
+    const TwSplit<lds_tw_lim(L)> tws{a.tw_col, twl};
     const unsigned tid = threadIdx.x;
     // tile fastest: an XCD runs neighbouring tiles of one item together, so
     // the cache lines they share meet in its L2
@@ -105,10 +106,10 @@ __global__ __launch_bounds__(PairShape<L>::NTH) void col_pair_kernel(SpectrumStr
     for (unsigned u = tid; u < 2 * kNB; u += NTH) pw[u / kNB][u % kNB] = 0.0;
     for (unsigned u = tid; u < kNB; u += NTH) coef[u] = a.coef[(int64_t)item * kNB + u];
     if constexpr (L >= 256)
-        for (unsigned i = tid; i < (unsigned)L; i += NTH) twl[i] = a.tw_col[i];
+        stage_twiddles<L, NTH>(twl, a.tw_col, tid);
     __syncthreads();
     const unsigned cid = tid / TPC, lane = tid % TPC;
-    if constexpr (L >= 256) col_forward_rest<L, TPC, A1>(lds + cid * SEG, lane, twl);
+    if constexpr (L >= 256) col_forward_rest<L, TPC, A1>(lds + cid * SEG, lane, tws);
     else stockham_fft<L, 1, TPC, false>(lds + cid * SEG, lane, a.tw_col);
 
     const int16_t* band = a.band + pr.pix_off;
@@ -203,8 +204,8 @@ __global__ __launch_bounds__(PairShape<L>::NTH) void col_pair_kernel(SpectrumStr
         }
     if constexpr (L >= 256) {
         // inverse transform, its last pass straight to HBM
-        col_inverse_head<L, TPC, AN>(lds + opaque(cid) * SEG, opaque(lane), twl + opaque(0u));
-        col_last_inverse<L, TC, NTH, SEG, AD>(lds, fld, W, opaque(tid), twl + opaque(0u), col_of);
+        col_inverse_head<L, TPC, AN>(lds + opaque(cid) * SEG, opaque(lane), opaque(tws));
+        col_last_inverse<L, TC, NTH, SEG, AD>(lds, fld, W, opaque(tid), opaque(tws), col_of);
     } else {
         stockham_fft<L, 1, TPC, true>(lds + opaque(cid) * SEG, opaque(lane), opaque(a.tw_col));
         for (unsigned e = tid; e < (unsigned)(TC * L); e += NTH) {

@@ -355,6 +355,11 @@ __global__ __launch_bounds__(kThreads) void row_kernel(SweepArgs a, int H) {
 //      natural-order row straight to HBM.
 // The same arithmetic, pass for pass and pixel for pixel, as row_kernel with
 // the plan of row_inverse / row_forward, so the two round identically.
+// The middle passes' twiddles are in LDS, the last passes' come coalesced from
+// L2.  2048^2 x 8 fields: 185 us, 240 when every pass gathered from one table
+// in L2 (537 MB of field, 76 us at a copy's rate; 125 us of vector issue, half
+// of it Philox); 1024^2 x 16: 75 us, 82 with that table in LDS, where its
+// strides collided in the banks.
 // Variants of the fused row kernel: pixel tables read in stage C (wide
 // launches, whose blocks hide the latency), read beside the field loads
 // (launches too small to fill the GPU), or either kind of item, a.packed
@@ -387,10 +392,7 @@ void row_kernel_f(SweepArgs a, int H) {
                                                                                  : pad_max(L, RM, RL, 16, AF);
     constexpr int LP = pad_len(L, AMAX);  // row stride in LDS
     __shared__ float2 lds[ROWS * LP];
-    // twiddles in LDS up to 1024 points (1024^2 -8%, 512^2 -6%, 256^2 -5% per
-    // sweep); at 2048 the extra 16 KiB would cost a resident block (+3%)
-    constexpr bool kTwLds = L <= 1024;
-    __shared__ float2 twl[kTwLds ? L : 1];
+    __shared__ float2 twl[lds_tw_len<L>()];
     static_assert(ROWS * LP >= kThreads, "residual partials fit in the rows");
     double* red = reinterpret_cast<double*>(lds);  // residual partials, once stage C has read the rows
     __shared__ int32_t row_item[ROWS], row_y[ROWS];
@@ -415,13 +417,7 @@ void row_kernel_f(SweepArgs a, int H) {
     // stage C go out beside the field loads, so that a block waits for memory
     // twice before it computes.
     const ItemDev it = a.items[item];
-    const float2* twr;
-    if constexpr (kTwLds) {
-        for (unsigned i = tid; i < (unsigned)L; i += kThreads) twl[i] = a.tw_row[i];
-        twr = twl;
-    } else {
-        twr = a.tw_row;
-    }
+    const auto twr = stage_twiddles<L, kThreads>(twl, a.tw_row, tid);
     const ProbDev pr{H, W, it.pix_off, it.tau, it.pid};
     float2* row = lds + rid * LP;
     const int64_t frow = it.field_off + (int64_t)y * W;
@@ -475,7 +471,7 @@ void row_kernel_f(SweepArgs a, int H) {
 #pragma unroll
             for (int r = 0; r < RL; ++r) v[i][r] = row[lpos_step<AC, NTL>(j, r)];
 #pragma unroll
-            for (int r = 1; r < RL; ++r) v[i][r] = cmulc(v[i][r], twr[r * j]);
+            for (int r = 1; r < RL; ++r) v[i][r] = cmulc(v[i][r], last_tw<L, RL>(twr, r, j));
             dft<RL, true>(v[i]);
             // v[i][r] is now the state at pixel x = j + r NTL
             if (a.emit_index >= 0 && valid) {
@@ -592,13 +588,13 @@ void row_kernel_f(SweepArgs a, int H) {
     }
 
     // ---- D: middle forward passes, then the last one (NS = L/16) to HBM
-    passes_before<L, RM, RL, 16, TPR, false, AF>(row, fresh(lane), twr + fresh(0u));
+    passes_before<L, RM, RL, 16, TPR, false, AF>(row, fresh(lane), opaque(twr));
     if (valid)
         with_storage(a.storage, [&](auto e0) {
             using E = decltype(e0);
             E* fld = reinterpret_cast<E*>(a.field) + frow;
             const unsigned lane2 = fresh(lane);
-            const float2* tw = twr + fresh(0u);
+            const auto tw = opaque(twr);
             float2 v[IT16][16];
 #pragma unroll
             for (int i = 0; i < IT16; ++i) {
@@ -607,7 +603,7 @@ void row_kernel_f(SweepArgs a, int H) {
 #pragma unroll
                     for (int r = 0; r < 16; ++r) v[i][r] = row[lpos_step<AD, NT16>(j, r)];
 #pragma unroll
-                    for (int r = 1; r < 16; ++r) v[i][r] = cmul(v[i][r], tw[r * j]);
+                    for (int r = 1; r < 16; ++r) v[i][r] = cmul(v[i][r], last_tw<L, 16>(tw, r, j));
                     dft<16, false>(v[i]);
 #pragma unroll
                     for (int r = 0; r < 16; ++r) fld[j + r * NT16] = narrow<E>(v[i][r]);
@@ -646,10 +642,7 @@ __global__ __launch_bounds__(NTH_) void col_kernel_t(SweepArgs a, int W) {
     constexpr int SEG = lds_stride<L>() + 32 / TC;
     constexpr int H = L;
     __shared__ float2 lds[TC * SEG];
-    // twiddles in LDS, or in L2 for 4-column tiles of 2048 rows (as in col_kernel_f; identical values)
-    constexpr bool kTwLds = !col_tw_in_l2(L, TC);
-    __shared__ float2 twl[kTwLds ? L : 1];
-    const float2* twp = kTwLds ? twl : a.tw_col;
+    __shared__ float2 twl[lds_tw_len<L>()];
     const unsigned tid = threadIdx.x;
     // tiles enumerated with the tile fastest: t = item * tiles + tile.  An
     // XCD then runs neighbouring tiles of one item together, and the cache
@@ -663,8 +656,7 @@ __global__ __launch_bounds__(NTH_) void col_kernel_t(SweepArgs a, int W) {
     const ProbDev pr = a.probs[it.prob];
     const int64_t f0 = it.field_off + x0;
 
-    if constexpr (kTwLds)
-        for (unsigned i = tid; i < (unsigned)L; i += NTH) twl[i] = a.tw_col[i];  // visible after the tile barrier
+    const auto twp = stage_twiddles<L, NTH>(twl, a.tw_col, tid);  // visible after the tile barrier
     with_storage(a.storage, [&](auto e0) {
         using E = decltype(e0);
         const E* fld = reinterpret_cast<const E*>(a.field) + f0;
@@ -742,7 +734,7 @@ __global__ __launch_bounds__(NTH_) void col_kernel_t(SweepArgs a, int W) {
         }
     }
     __syncthreads();
-    stockham_fft<L, 1, TPC, true>(lds + fresh(cid) * SEG, fresh(lane), twp + fresh(0u));
+    stockham_fft<L, 1, TPC, true>(lds + fresh(cid) * SEG, fresh(lane), opaque(twp));
 
     with_storage(a.storage, [&](auto e0) {
         using E = decltype(e0);
@@ -767,9 +759,11 @@ __global__ __launch_bounds__(NTH_) void col_kernel_t(SweepArgs a, int W) {
 //      the column-pair table nPt gives both coefficients in one coalesced load;
 //   D. the middle inverse passes run in LDS and the last one writes its
 //      outputs, in natural order, straight to HBM.
-// The twiddle table sits in LDS beside the tile (16 KiB at 2048 rows): with
-// one or two workgroups per CU every wave waits for the same twiddles, and an
-// LDS read returns much sooner than an L2 hit (2048^2 sweep -6%, 1024^2 -10%).
+// The middle passes' twiddles sit in LDS beside the tile, the last passes' come
+// from L2, a cache line or four per load (lds_tw_lim).
+// Bound by L2 and HBM requests of TC 8-byte values a row: 2048^2 x 8 fields
+// 249 us for 537 MB (a plain copy in these tiles 86 us) and 1024^2 x 16 fields
+// 76 us, before the pass tables 269 and 82.
 // Same arithmetic per mode as col_kernel_t, with the plan of the row kernels
 // (forward 16, RM..., RL; inverse RL, RM..., 16).  Every sweep of a run takes
 // the same column kernel, so split runs still repeat uninterrupted ones.
@@ -790,7 +784,7 @@ __global__ __launch_bounds__(NTH_) void col_kernel_f(SweepArgs a, int W) {
     constexpr int PMAX = pad_max(L, RM, 16, RL, P1) > pad_max(L, RM, RL, 16, PF) ? pad_max(L, RM, 16, RL, P1)
                                                                                  : pad_max(L, RM, RL, 16, PF);
     constexpr int PSEG = tile_seg(TC, P1, pad_after(L, RM, RL, 16, PF), pad_len(L, PMAX));
-    constexpr int kExtra = col_tw_in_l2(L, TC) ? 0 : 8 * L;
+    constexpr int kExtra = 8 * lds_tw_len<L>();
     constexpr bool kPad = lds_keeps_blocks(TC * (L + 32 / TC) * 8 + kExtra, TC * PSEG * 8 + kExtra);
     constexpr int A1 = kPad ? P1 : -1, AC = pad_after(L, RM, 16, RL, A1);
     constexpr int AF = kPad ? PF : -1, AD = pad_after(L, RM, RL, 16, AF);
@@ -802,13 +796,7 @@ __global__ __launch_bounds__(NTH_) void col_kernel_f(SweepArgs a, int W) {
     constexpr int ITL = (NTL + TPP - 1) / TPP;
     static_assert(L >= 256 && TC % 2 == 0 && NTH % (TC / 2) == 0, "col_kernel_f shape");
     __shared__ float2 lds[TC * SEG];
-    // twiddles W_H^r in LDS: LDS latency instead of L2's for every pass; the
-    // 4-column tiles of 2048 rows (the default there) read them from L2
-    // instead, so that two workgroups fit in a CU's LDS and one's memory
-    // phases overlap the other's (2048^2 sweep -3.5%)
-    constexpr bool kTwLds = !col_tw_in_l2(L, TC);
-    __shared__ float2 twl[kTwLds ? L : 1];
-    const float2* twp = kTwLds ? twl : a.tw_col;
+    __shared__ float2 twl[lds_tw_len<L>()];
     const unsigned tid = threadIdx.x;
     const int64_t t = xcd_block(blockIdx.x, gridDim.x);
     const int item = (int)(t / (W / TC));
@@ -817,8 +805,7 @@ __global__ __launch_bounds__(NTH_) void col_kernel_f(SweepArgs a, int W) {
     // offset, tau and index); the twiddles go out beside it and the mode
     // table of phase C beside the field loads
     const ItemDev it = a.items[item];
-    if constexpr (kTwLds)
-        for (unsigned i = tid; i < (unsigned)L; i += NTH) twl[i] = a.tw_col[i];  // visible after phase A's barrier
+    const auto twp = stage_twiddles<L, NTH>(twl, a.tw_col, tid);  // visible after phase A's barrier
     const ProbDev pr{H, W, it.pix_off, it.tau, it.pid};
     const int64_t f0 = it.field_off + x0;
     float2 pnp[ITL][RL];
@@ -884,7 +871,7 @@ __global__ __launch_bounds__(NTH_) void col_kernel_f(SweepArgs a, int W) {
                     for (int r = 0; r < RL; ++r) v[i][q][r] = lds[(2 * pp + q) * SEG + lpos_step<AC, NTL>(j, r)];
 #pragma unroll
                 for (int r = 1; r < RL; ++r) {
-                    const float2 w = twp[r * j];
+                    const float2 w = last_tw<L, RL>(twp, r, j);
                     v[i][0][r] = cmul(v[i][0][r], w);
                     v[i][1][r] = cmul(v[i][1][r], w);
                 }
@@ -939,13 +926,13 @@ __global__ __launch_bounds__(NTH_) void col_kernel_f(SweepArgs a, int W) {
     // ---- D: middle inverse passes, then the last one (NS = L/16) to HBM
     {
         const unsigned cid = fresh(tid) / TPC, lane = fresh(tid) % TPC;
-        passes_before<L, RM, RL, 16, TPC, true, AF>(lds + cid * SEG, lane, twp + fresh(0u));
+        passes_before<L, RM, RL, 16, TPC, true, AF>(lds + cid * SEG, lane, opaque(twp));
     }
     with_storage(a.storage, [&](auto e0) {
         using E = decltype(e0);
         E* fld = reinterpret_cast<E*>(a.field) + f0;
         const unsigned tid2 = fresh(tid);
-        const float2* tw = twp + fresh(0u);
+        const auto tw = opaque(twp);
         float2 v[IT16][16];
 #pragma unroll
         for (int i = 0; i < IT16; ++i) {
@@ -955,7 +942,7 @@ __global__ __launch_bounds__(NTH_) void col_kernel_f(SweepArgs a, int W) {
 #pragma unroll
                 for (int r = 0; r < 16; ++r) v[i][r] = lds[c * SEG + lpos_step<AD, NT16>(j, r)];
 #pragma unroll
-                for (int r = 1; r < 16; ++r) v[i][r] = cmulc(v[i][r], tw[r * j]);
+                for (int r = 1; r < 16; ++r) v[i][r] = cmulc(v[i][r], last_tw<L, 16>(tw, r, j));
                 dft<16, true>(v[i]);
 #pragma unroll
                 for (int r = 0; r < 16; ++r) fld[(int64_t)(j + r * NT16) * W + c] = narrow<E>(v[i][r]);

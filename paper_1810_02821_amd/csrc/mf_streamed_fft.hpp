@@ -8,27 +8,48 @@
 
 namespace mf {
 
-// Transform plan of the fused streamed kernels: a radix-16 pass at one end,
-// a radix-RL pass at the other, radix-RM passes between them.  L = 256 uses
-// 16 x 4 x 4, so that its RL pass has enough butterflies for every lane and
-// holds few values per thread; longer transforms use radix 16 and the
-// remainder (2048 = 16 x 16 x 8).
 template <int L>
-constexpr int last_radix() {
-    if (L == 256) return 4;
-    int r = L;
-    while (r > 16) r /= 16;
-    return r;
+constexpr int last_radix() { return last_radix_of(L); }
+template <int L>
+constexpr int middle_radix() { return middle_radix_of(L); }
+
+// Largest NS whose pass tables the streamed kernels copy to LDS; the later
+// ones (from 1024 points only those of the last passes) are read from L2, one
+// coalesced load per twiddle.  All tables in LDS cost resident workgroups, none
+// there exposes L2's latency in the middle passes (us per sweep kernel, FP32,
+// none / these / all in LDS; 2048^2 x 8 and 1024^2 x 16 fields: rows 213 / 185
+// / 298 and 91 / 75 / 98, columns 249 / 247 / - and 80 / 76 / 83).
+constexpr int lds_tw_lim(int L) { return L >= 1024 && is_pow2(L) ? 16 : L == 512 ? 32 : L == 256 ? 16 : L; }
+// Copy them (visible after the caller's next barrier).
+template <int L, int NTH, int LIM = lds_tw_lim(L)>
+__device__ __forceinline__ TwSplit<LIM> stage_twiddles(float2* twl, const float2* tw, unsigned tid) {
+    constexpr unsigned n = pass_prefix(L, LIM);
+    for (unsigned i = tid; i < n; i += NTH) twl[i] = tw[i];
+    return {tw, twl};
+}
+// The same pointers behind asm (the compiler then does not keep the forward
+// transform's twiddles and addresses live into the inverse one).
+template <int LIM>
+__device__ __forceinline__ TwSplit<LIM> opaque(TwSplit<LIM> t) {
+    unsigned zero = 0;
+    asm volatile("" : "+s"(t.g), "+v"(zero));
+    return {t.g, t.l + zero};
 }
 template <int L>
-constexpr int middle_radix() { return L == 256 ? 4 : 16; }
+constexpr int lds_tw_len() { return pass_prefix(L, lds_tw_lim(L)) > 0 ? pass_prefix(L, lds_tw_lim(L)) : 1; }
+
+// Twiddle W_L^{r j} of the last radix-R pass (NS = L / R), from the pass tables.
+template <int L, int R, typename TW>
+__device__ __forceinline__ float2 last_tw(const TW& tw, int r, unsigned j) {
+    return pass_table<L, R, L / R>(tw)[(r - 1) * (L / R) + j];
+}
 
 // Radix-RM Stockham passes over LDS with NS = NS0, RM NS0, ... while
 // NS * RM * TAIL <= L and NS * TAIL < L: all passes before a final pass of
 // radix TAIL.  The first pass reads layout AI; with AI >= 0 every pass writes
 // the padded layout pad_of picks for it, otherwise the XOR swizzle.
-template <int L, int RM, int NS, int TAIL, int TPG, bool INV, int AI = -1>
-__device__ __forceinline__ void passes_before(float2* buf, unsigned lane, const float2* __restrict__ tw) {
+template <int L, int RM, int NS, int TAIL, int TPG, bool INV, int AI = -1, typename TW>
+__device__ __forceinline__ void passes_before(float2* buf, unsigned lane, const TW& tw) {
     if constexpr (NS * RM * TAIL <= L && NS * TAIL < L) {
         constexpr int AO = AI >= 0 ? pad_of(L, RM, NS) : -1;
         stockham_pass<L, RM, NS, TPG, INV, AI, AO>(buf, lane, tw);
@@ -163,8 +184,8 @@ __device__ __forceinline__ void col_first_forward(float2* lds, const float2* fld
         }
     }
 }
-template <int L, int TPC, int A1 = -1>
-__device__ __forceinline__ void col_forward_rest(float2* buf, unsigned lane, const float2* __restrict__ tw) {
+template <int L, int TPC, int A1 = -1, typename TW>
+__device__ __forceinline__ void col_forward_rest(float2* buf, unsigned lane, const TW& tw) {
     constexpr int RL = last_radix<L>(), RM = middle_radix<L>();
     constexpr int AC = pad_after(L, RM, 16, RL, A1);
     constexpr int AN = A1 >= 0 ? pad_of(L, RL, L / RL) : -1;
@@ -173,16 +194,16 @@ __device__ __forceinline__ void col_forward_rest(float2* buf, unsigned lane, con
 }
 // Inverse counterpart: radix RL, RM... in LDS, then the last radix-16 pass
 // writes natural-order rows straight to HBM.
-template <int L, int TPC, int AN = -1>
-__device__ __forceinline__ void col_inverse_head(float2* buf, unsigned lane, const float2* __restrict__ tw) {
+template <int L, int TPC, int AN = -1, typename TW>
+__device__ __forceinline__ void col_inverse_head(float2* buf, unsigned lane, const TW& tw) {
     constexpr int RL = last_radix<L>();
     constexpr int AF = AN >= 0 ? pad_of(L, RL, 1) : -1;
     stockham_pass<L, RL, 1, TPC, true, AN, AF>(buf, lane, tw);
     passes_before<L, middle_radix<L>(), RL, 16, TPC, true, AF>(buf, lane, tw);
 }
-template <int L, int TC, int NTH, int SEG, int AD = -1, typename ColOf>
-__device__ __forceinline__ void col_last_inverse(const float2* lds, float2* fld, int W, unsigned tid,
-                                                 const float2* __restrict__ tw, ColOf col_of) {
+template <int L, int TC, int NTH, int SEG, int AD = -1, typename TW, typename ColOf>
+__device__ __forceinline__ void col_last_inverse(const float2* lds, float2* fld, int W, unsigned tid, const TW& tw,
+                                                 ColOf col_of) {
     constexpr int NT16 = L / 16;
     constexpr int IT16 = (TC * NT16 + NTH - 1) / NTH;
 #pragma unroll
@@ -195,7 +216,7 @@ __device__ __forceinline__ void col_last_inverse(const float2* lds, float2* fld,
 #pragma unroll
             for (int r = 0; r < 16; ++r) v[r] = lds[c * SEG + lpos_step<AD, NT16>(j, r)];
 #pragma unroll
-            for (int r = 1; r < 16; ++r) v[r] = cmulc(v[r], tw[r * j]);
+            for (int r = 1; r < 16; ++r) v[r] = cmulc(v[r], last_tw<L, 16>(tw, r, j));
             dft<16, true>(v);
 #pragma unroll
             for (int r = 0; r < 16; ++r) fld[(int64_t)(j + r * NT16) * W + col] = v[r];
