@@ -128,6 +128,11 @@ struct mf_plan_s {
     };
     std::vector<GraphEntry> graphs;
     hipStream_t cap_stream = nullptr;
+    // streams beside the caller's for the size classes of one mf_sample call,
+    // with the events that order them after and before the caller's work
+    static constexpr int kSides = 3;
+    hipStream_t side[kSides] = {};
+    hipEvent_t fork = nullptr, joined[kSides] = {};
     std::vector<float> host_nbar;    // for residual norms
     bool has_response = false;       // some problem has a diagonal A != I
     float* d_rinv = nullptr;         // 1 / A_i per pixel (0 without response), when has_response
@@ -178,6 +183,11 @@ struct mf_plan_s {
             if (g.graph) (void)hipGraphDestroy(g.graph);
         }
         if (cap_stream) (void)hipStreamDestroy(cap_stream);
+        if (fork) (void)hipEventDestroy(fork);
+        for (int i = 0; i < kSides; ++i) {
+            if (joined[i]) (void)hipEventDestroy(joined[i]);
+            if (side[i]) (void)hipStreamDestroy(side[i]);
+        }
     }
 };
 
@@ -504,12 +514,10 @@ mf_status ws(DevBuf& b, size_t bytes, hipStream_t s) {
     return MF_OK;
 }
 
-// Items workspace for work lists of up to `per` items per problem (two
-// regions: the list and, for residual tests, the converged subset).
+// Items workspace for work lists of `per` items per problem: room for a list
+// per size class (or, for residual tests, one list and its converged subset).
 mf_status ensure_items(mf_plan p, int per, hipStream_t s) {
-    size_t max_items = 0;
-    for (auto& kv : p->classes) max_items = std::max(max_items, kv.second.size() * (size_t)per);
-    return ws(p->items, 2 * (max_items + 1) * sizeof(mf::ItemDev), s);
+    return ws(p->items, 2 * (p->probs.size() * (size_t)per + 1) * sizeof(mf::ItemDev), s);
 }
 
 // Build the work list of size class `cls` on the device: `per` items per
@@ -1459,8 +1467,60 @@ struct SampleWs {
     float4* coef = nullptr;        // persistent tables: 40 bytes per pixel pair
     float* dprime = nullptr;       // d / A (response plans)
     float2* field = nullptr;       // work field when state_out is NULL
+    float2* packed = nullptr;      // fields of the packed classes, one after another (none: they run unpacked)
     float2* hfield = nullptr;      // 16-bit work field (4 bytes per element)
     bool graphs = true;            // MF_FLAG_GRAPH may capture and instantiate graphs (which allocates)
+    bool overlap = true;           // `items` holds a list per size class, so that classes may run side by side
+};
+
+// The streams of one call's size classes: class i takes the caller's stream or
+// one of the plan's, ordered after the caller's work so far; join() (or the
+// destructor, on an error's way out) orders the caller's later work after all.
+struct ClassStreams {
+    mf_plan p;
+    hipStream_t s;
+    bool on;
+    bool used[mf_plan_s::kSides] = {};
+    ClassStreams(mf_plan plan, hipStream_t stream, bool overlap) : p(plan), s(stream), on(overlap) {}
+    // Create what the plan's classes need (the first call does, or mf_plan_reserve).
+    static hipError_t prepare(mf_plan p) {
+        hipError_t e = hipSuccess;
+        if (!p->fork) e = hipEventCreateWithFlags(&p->fork, hipEventDisableTiming);
+        for (int k = 0; k < mf_plan_s::kSides && k + 1 < (int)p->classes.size(); ++k) {
+            if (e == hipSuccess && !p->side[k]) e = hipStreamCreateWithFlags(&p->side[k], hipStreamNonBlocking);
+            if (e == hipSuccess && !p->joined[k]) e = hipEventCreateWithFlags(&p->joined[k], hipEventDisableTiming);
+        }
+        return e;
+    }
+    hipError_t open() {
+        if (!on) return hipSuccess;
+        const hipError_t e = prepare(p);
+        return e == hipSuccess ? hipEventRecord(p->fork, s) : e;
+    }
+    hipError_t of(int i, hipStream_t* out) {
+        *out = s;
+        const int k = i % (mf_plan_s::kSides + 1) - 1;
+        if (!on || k < 0) return hipSuccess;
+        if (!used[k]) {
+            const hipError_t e = hipStreamWaitEvent(p->side[k], p->fork, 0);
+            if (e != hipSuccess) return e;
+        }
+        used[k] = true;
+        *out = p->side[k];
+        return hipSuccess;
+    }
+    hipError_t join() {
+        hipError_t r = hipSuccess;
+        for (int k = 0; k < mf_plan_s::kSides; ++k) {
+            if (!used[k]) continue;
+            used[k] = false;
+            hipError_t e = hipEventRecord(p->joined[k], p->side[k]);
+            if (e == hipSuccess) e = hipStreamWaitEvent(s, p->joined[k], 0);
+            if (r == hipSuccess) r = e;
+        }
+        return r;
+    }
+    ~ClassStreams() { (void)join(); }
 };
 
 mf_status validate_sample(const mf_sample_args* g, const float* state_out, const float* samples_out) {
@@ -1496,12 +1556,14 @@ mf_status ensure_sample_workspace(mf_plan p, int pairs, int storage, int form, b
     if (st != MF_OK) return st;
     const size_t field_elems = (size_t)p->total_px * pairs;
     // single-chain problems on the streamed kernels run packed two to a field,
-    // in a workspace field whatever state_out is
-    bool packs = false;
+    // in fields of their own after the work field
+    size_t packed = 0;
     if (pairs == 1 && storage == MF_STORAGE_FP32)
         for (auto& kv : p->classes)
-            packs |= kv.second.size() >= 2 && !mf::resident_supported(kv.first.first, kv.first.second);
-    if ((need_field || packs) && (st = ws(p->field, field_elems * sizeof(float2), s)) != MF_OK) return st;
+            if (kv.second.size() >= 2 && (form == MF_FORM_STREAMED || !mf::resident_supported(kv.first.first, kv.first.second)))
+                packed += (kv.second.size() + 1) / 2 * (size_t)kv.first.first * kv.first.second;
+    const size_t elems = (need_field ? field_elems : 0) + packed;
+    if (elems && (st = ws(p->field, elems * sizeof(float2), s)) != MF_OK) return st;
     if (storage != MF_STORAGE_FP32 && (st = ws(p->hfield, field_elems * 4, s)) != MF_OK) return st;
     if (sample_any_persistent(p, form) &&
         (st = ws(p->coef, (size_t)p->total_px / 2 * (sizeof(float4) + sizeof(float2) + sizeof(float4)), s)) != MF_OK)
@@ -1550,8 +1612,19 @@ mf_status sample_impl(mf_plan p, const float* d, const mf_sample_args* g, const 
                                         true, s));
     }
     if (g->check_finite) MF_HIP(mf::launch_fill_int(p->d_flag, INT32_MAX, 1, s));
+    // Size classes share nothing but read-only tables and the flag's minimum, and
+    // one class's launches seldom fill the GPU (192 problems of four sizes, one
+    // chain each: 6.68 ms one class after another, 4.20 ms side by side).  A stream
+    // being captured keeps the sequence.
+    ClassStreams cls(p, s, w.overlap && p->classes.size() > 1 && !capturing(s));
+    MF_HIP(cls.open());
+    mf::ItemDev* items = w.items;
+    float2* pfield = w.packed;
+    int n_cls = 0;
     for (auto& kv : p->classes) {
         const int H = kv.first.first, W = kv.first.second;
+        hipStream_t s = nullptr;
+        MF_HIP(cls.of(n_cls++, &s));
         int form = g->form;
         if (form == MF_FORM_AUTO) form = mf::resident_supported(H, W) ? MF_FORM_PERSISTENT : MF_FORM_STREAMED;
         if (form == MF_FORM_PERSISTENT && !mf::resident_supported(H, W))
@@ -1560,29 +1633,33 @@ mf_status sample_impl(mf_plan p, const float* d, const mf_sample_args* g, const 
         // complex field (no imaginary chain computed only to be dropped)
         const int n_pids = (int)kv.second.size();
         const bool packed = form == MF_FORM_STREAMED && g->chains_per_problem == 1 && g->storage == MF_STORAGE_FP32 &&
-                            n_cool == 0 && n_pids >= 2 && w.field && is_pow2(H) && is_pow2(W);
+                            n_cool == 0 && n_pids >= 2 && pfield && is_pow2(H) && is_pow2(W);
         mf::ItemDev* di = nullptr;
         int n_items = 0;
         mf_status st = MF_OK;
         if (packed) {
             n_items = (n_pids + 1) / 2;
-            if ((size_t)n_items > w.items_cap) return fail(MF_ERR_INVALID_ARG, "internal: items workspace too small");
-            di = w.items;
+            if ((size_t)(items - w.items) + n_items > w.items_cap)
+                return fail(MF_ERR_INVALID_ARG, "internal: items workspace too small");
+            di = items;
             MF_HIP(mf::launch_fill_packed_items(di, p->d_probs, p->d_class_pids + p->class_all.at(kv.first).first, n_pids,
                                                 (int64_t)H * W, s));
-            st = sample_streamed(p, di, n_items, H, W, d, &gm, w.field, sin, samples_out, w.graphs, true, s);
+            st = sample_streamed(p, di, n_items, H, W, d, &gm, pfield, sin, samples_out, w.graphs, true, s);
             if (st != MF_OK) return st;
             mf::SweepArgs a = base_args(p, H, W);
             a.items = di;
             a.n_items = n_items;
-            a.field = w.field;
+            a.field = pfield;
             a.packed = 1;
             if (state_out) MF_HIP(mf::launch_pack_copy_out(W, H, a, work, s));
             if (g->check_finite) MF_HIP(mf::launch_finite_check(W, H, a, p->d_flag, s));
+            if (w.overlap) items += n_items;
+            pfield += (size_t)n_items * H * W;
             continue;
         }
-        st = class_items_at(p, w.items, w.items_cap, kv.first, pairs, false, false, s, &di, &n_items);
+        st = class_items_at(p, items, w.items_cap - (items - w.items), kv.first, pairs, false, false, s, &di, &n_items);
         if (st != MF_OK) return st;
+        if (w.overlap) items += n_items;
         const float2* cin = sin;  // the state the sampling phase starts from
         if (n_cool > 0) {
             float2* cw = (form != MF_FORM_PERSISTENT && hwork) ? hwork : work;
@@ -1641,6 +1718,7 @@ mf_status sample_impl(mf_plan p, const float* d, const mf_sample_args* g, const 
         // state (every sweep mixes all pixels through the transforms)
         if (g->check_finite) MF_HIP(mf::launch_finite_check(W, H, chk, p->d_flag, s));
     }
+    MF_HIP(cls.join());
     return g->check_finite ? read_finite_flag(p, s) : MF_OK;
 }
 
@@ -1973,8 +2051,10 @@ mf_status mf_plan_reserve(mf_plan p, const mf_reserve* r) {
         if ((st = ensure_loss_workspace(p, s)) != MF_OK) return st;
     }
     if ((r->calls & MF_RESERVE_SAMPLE) &&
-        (st = ensure_sample_workspace(p, pairs, r->storage, MF_FORM_AUTO, true, s)) != MF_OK)
+        ((st = ensure_sample_workspace(p, pairs, r->storage, MF_FORM_AUTO, true, s)) != MF_OK ||
+         (st = ensure_sample_workspace(p, pairs, r->storage, MF_FORM_STREAMED, true, s)) != MF_OK))
         return st;
+    if ((r->calls & MF_RESERVE_SAMPLE) && p->classes.size() > 1) MF_HIP(ClassStreams::prepare(p));
     if ((r->calls & MF_RESERVE_SPECTRUM) && (st = ensure_spectrum_workspace(p, pairs, true, s)) != MF_OK) return st;
     if ((r->calls & MF_RESERVE_SHEAR) &&
         (st = ensure_shear_workspace(p, r->chains_per_problem, true, true, true, s)) != MF_OK)
@@ -2286,6 +2366,7 @@ mf_status mf_sample(mf_plan p, const float* d, const mf_sample_args* g, const fl
     w.coef = p->coef.as<float4>();
     w.dprime = p->dprime.as<float>();
     w.field = p->field.as<float2>();
+    w.packed = pairs == 1 && w.field ? w.field + (state_out ? 0 : p->total_px) : nullptr;
     w.hfield = p->hfield.as<float2>();
     return sample_impl(p, d, g, state_in, state_out, samples_out, w, s);
 }
@@ -2323,6 +2404,7 @@ mf_status mf_sample_noalloc(mf_plan p, const float* d, const mf_sample_args* g, 
     w.dprime = dp_b ? reinterpret_cast<float*>(base + items_b + coef_b) : nullptr;
     w.hfield = hf_b ? reinterpret_cast<float2*>(base + items_b + coef_b + dp_b) : nullptr;
     w.graphs = false;
+    w.overlap = false;
     return sample_impl(p, d, g, state_in, state_out, samples_out, w, (hipStream_t)stream);
 }
 
