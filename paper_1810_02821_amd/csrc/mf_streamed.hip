@@ -1519,7 +1519,8 @@ hipError_t launch_row(int W, int H, int row_mode, const SweepArgs& a, hipStream_
         hipLaunchKernelGGL((col_kernel_t<LL, TCC, NN>), grid, dim3(NN), 0, s, a, W);           \
         return hipGetLastError();                                                              \
     }
-// H >= 256 without the gradient's stored transforms: the fused kernel
+// H >= 256 without the gradient's stored transforms, in whole tiles: the fused
+// kernel (a ragged last tile, W a multiple of 2 3^b, is col_kernel_t's)
 #define MF_COL_CASE_F(LL, TCC, NN)                                                            \
     if (H == LL && tc == TCC && nth == NN) {                                                   \
         if (fused)                                                                             \
@@ -1532,7 +1533,7 @@ hipError_t launch_row(int W, int H, int row_mode, const SweepArgs& a, hipStream_
 hipError_t launch_col_shape(int W, int H, int tc, int nth, const SweepArgs& a, hipStream_t s) {
     if (tc < 2) return hipErrorInvalidValue;
     const dim3 grid((unsigned)((int64_t)a.n_items * ((W + tc - 1) / tc)));
-    const bool fused = !a.t_store && !a.t_load && a.nPt && !a.plain_kernels;
+    const bool fused = !a.t_store && !a.t_load && a.nPt && !a.plain_kernels && W % tc == 0;
     MF_COL_CASE(16, 16, 256) MF_COL_CASE(32, 16, 256) MF_COL_CASE(64, 16, 256) MF_COL_CASE(128, 16, 256)
     MF_COL_CASE_F(256, 16, 256) MF_COL_CASE_F(256, 8, 256) MF_COL_CASE_F(256, 16, 512) MF_COL_CASE_F(256, 8, 512)
     MF_COL_CASE_F(256, 4, 128) MF_COL_CASE_F(256, 4, 256)
