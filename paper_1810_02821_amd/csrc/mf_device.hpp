@@ -214,6 +214,19 @@ __device__ __forceinline__ const float2* pass_table(const TwSplit<LIM>& tw) {
     if constexpr (NS <= LIM) return pass_table<L, R, NS>(tw.l);
     else return pass_table<L, R, NS>(tw.g);
 }
+// The table W_L^r itself in LDS, half the size of the pass tables.
+struct TwBase {
+    const float2* l;
+};
+// Twiddle W_{R NS}^{r k} of a radix-R pass after NS points, k = j mod NS.
+template <int L, int R, int NS, typename TW>
+__device__ __forceinline__ float2 pass_twiddle(const TW& tw, int r, unsigned k) {
+    return (pass_table<L, R, NS>(tw) + k)[(r - 1) * NS];
+}
+template <int L, int R, int NS>
+__device__ __forceinline__ float2 pass_twiddle(const TwBase& tw, int r, unsigned k) {
+    return tw.l[(r * k) * (L / (NS * R))];
+}
 
 // One radix-R pass of a length-L transform held in `buf`, reading the
 // exchange in layout AI and writing in layout AO.  `lane` in [0, TPG)
@@ -235,10 +248,10 @@ __device__ __forceinline__ void stockham_pass(float2* buf, unsigned lane, const 
 #pragma unroll
             for (int r = 0; r < R; ++r) v[t][r] = buf[lpos_step<AI, NT>(j, r)];
             if constexpr (NS > 1) {
-                const float2* wk = pass_table<L, R, NS>(tw) + j % NS;
+                const unsigned k = j % NS;
 #pragma unroll
                 for (int r = 1; r < R; ++r) {
-                    const float2 w = wk[(r - 1) * NS];
+                    const float2 w = pass_twiddle<L, R, NS>(tw, r, k);
                     v[t][r] = INV ? cmulc(v[t][r], w) : cmul(v[t][r], w);
                 }
             }
@@ -277,10 +290,9 @@ __device__ __forceinline__ void group_stages(float2 (&v)[P], unsigned k1, const 
 #pragma unroll
                 for (int r = 0; r < R; ++r) x[r] = v[c + Q * (m + M * r)];
                 if constexpr (NC > 1) {
-                    const float2* wk = pass_table<L, R, NC>(tw) + k1 + c * NS;
 #pragma unroll
                     for (int r = 1; r < R; ++r) {
-                        const float2 w = wk[(r - 1) * NC];
+                        const float2 w = pass_twiddle<L, R, NC>(tw, r, k1 + c * NS);
                         x[r] = INV ? cmulc(x[r], w) : cmul(x[r], w);
                     }
                 }

@@ -52,7 +52,7 @@ struct SweepArgs {
     const float* nbar;        // concatenated Nbar (+inf missing)
     const float* nP;          // concatenated n P(|k|) per mode (unshifted order)
     const float2* nPt;        // column-pair table: [pix_off/2 + (kx/2) H + ky] = (nP(ky,kx), nP(ky,kx+1)), or null
-    const float2* tw_row;     // pass tables of W (pass_plan)
+    const float2* tw_row;     // pass tables of W (pass_plan), W_W^r 2 W entries before them
     const float2* tw_col;     // pass tables of H
     float lambda;             // cooling level: T = lambda * tau
     int32_t stochastic;       // 1: draw variates (sampler), 0: Wiener iteration

@@ -35,13 +35,18 @@ __device__ __forceinline__ TwSplit<LIM> opaque(TwSplit<LIM> t) {
     asm volatile("" : "+s"(t.g), "+v"(zero));
     return {t.g, t.l + zero};
 }
+__device__ __forceinline__ TwBase opaque(TwBase t) {
+    unsigned zero = 0;
+    asm volatile("" : "+v"(zero));
+    return {t.l + zero};
+}
 template <int L>
 constexpr int lds_tw_len() { return pass_prefix(L, lds_tw_lim(L)) > 0 ? pass_prefix(L, lds_tw_lim(L)) : 1; }
 
 // Twiddle W_L^{r j} of the last radix-R pass (NS = L / R), from the pass tables.
 template <int L, int R, typename TW>
 __device__ __forceinline__ float2 last_tw(const TW& tw, int r, unsigned j) {
-    return pass_table<L, R, L / R>(tw)[(r - 1) * (L / R) + j];
+    return pass_twiddle<L, R, L / R>(tw, r, j);
 }
 
 // Radix-RM Stockham passes over LDS with NS = NS0, RM NS0, ... while
