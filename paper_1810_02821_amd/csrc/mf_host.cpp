@@ -143,7 +143,10 @@ struct mf_plan_s {
     std::map<std::pair<int, int>, std::pair<int, int>> class_all, class_band;
     int32_t* d_band_modes = nullptr;  // modes per band, concatenated
     double* d_band_amps = nullptr;    // the plan's band amplitudes, concatenated
-    int32_t* d_flag = nullptr;        // non-finite check: lowest problem index with a non-finite state
+    // non-finite check (FiniteFlag): device word (behind d_probs), pinned host word, number of the last checked call
+    unsigned long long* d_flag = nullptr;
+    uint32_t* h_flag = nullptr;
+    uint32_t checked_calls = 0;
     DevBuf lossbuf;                   // mf_band_loss: grad_s, explicit grad_d, partial sums, band powers
     ~mf_plan_s() {
         (void)hipFree(d_probs);
@@ -159,7 +162,7 @@ struct mf_plan_s {
         (void)hipFree(d_class_pids);
         (void)hipFree(d_band_modes);
         (void)hipFree(d_band_amps);
-        (void)hipFree(d_flag);
+        if (h_flag) (void)hipHostFree(h_flag);
         dprime.release();
         lossbuf.release();
         for (auto& kv : d_tw) (void)hipFree(kv.second);
@@ -193,7 +196,8 @@ struct mf_plan_s {
 
 namespace {
 
-mf_status read_finite_flag(mf_plan p, hipStream_t s);
+mf_status finite_flag(mf_plan p, bool check, hipStream_t s, mf::FiniteFlag* f);
+mf_status read_finite_flag(mf_plan p, mf::FiniteFlag f, hipStream_t s);
 
 // P(|k|) of one problem, evaluated in FP64 (Eq. 9).
 double spectrum_at(const HostProblem& p, double k) {
@@ -917,12 +921,12 @@ mf_status ensure_shear_workspace(mf_plan p, int chains, bool field, bool check, 
 }
 
 hipError_t shear_check_class(mf_plan p, int H, int W, const mf::ItemDev* di, int n_items, float* fin,
-                             hipStream_t s) {
+                             mf::FiniteFlag flag, hipStream_t s) {
     mf::SweepArgs c = base_args(p, H, W);
     c.items = di;
     c.n_items = n_items;
     c.field = reinterpret_cast<float2*>(fin);
-    return mf::launch_finite_check(W, H, c, p->d_flag, s);
+    return mf::launch_finite_check(W, H, c, flag, s);
 }
 
 mf_status launch_shear(mf_plan p, const float* gamma, float b_ratio, int chains, const std::vector<double>& lam,
@@ -934,7 +938,8 @@ mf_status launch_shear(mf_plan p, const float* gamma, float b_ratio, int chains,
     if (st != MF_OK) return st;
     // the chains' final states: the caller's, or the plan field (streamed classes, non-finite check)
     float* fin = state_out ? state_out : reinterpret_cast<float*>(p->field.as<float2>());
-    if (check) MF_HIP(mf::launch_fill_int(p->d_flag, INT32_MAX, 1, s));
+    mf::FiniteFlag flag;
+    if ((st = finite_flag(p, check, s, &flag)) != MF_OK) return st;
     for (auto& kv : p->classes) {
         const int N = kv.first.first, W = kv.first.second;
         mf::ItemDev* di = nullptr;
@@ -944,7 +949,7 @@ mf_status launch_shear(mf_plan p, const float* gamma, float b_ratio, int chains,
             st = shear_streamed(p, di, n_items, N, W, gamma, b_ratio, chains, lam, sweeps, stochastic, seed,
                                 sweep_offset, burn_in, n_samples, thin, state_in, state_out, samples, kappa_out, s);
             if (st != MF_OK) return st;
-            if (check) MF_HIP(shear_check_class(p, N, W, di, n_items, fin, s));
+            if (check) MF_HIP(shear_check_class(p, N, W, di, n_items, fin, flag, s));
             continue;
         }
         if (L > mf::kMaxLevels)
@@ -976,9 +981,9 @@ mf_status launch_shear(mf_plan p, const float* gamma, float b_ratio, int chains,
         r.state_out = check ? reinterpret_cast<float2*>(fin) : reinterpret_cast<float2*>(state_out);
         r.kappa_out = reinterpret_cast<float2*>(kappa_out);
         MF_HIP(mf::launch_resident_shear(N, r, s));
-        if (check) MF_HIP(shear_check_class(p, N, W, di, n_items, fin, s));
+        if (check) MF_HIP(shear_check_class(p, N, W, di, n_items, fin, flag, s));
     }
-    return check ? read_finite_flag(p, s) : MF_OK;
+    return check ? read_finite_flag(p, flag, s) : MF_OK;
 }
 
 // Real part of the field buffer of one streamed size class into `out`.
@@ -1572,15 +1577,30 @@ mf_status ensure_sample_workspace(mf_plan p, int pairs, int storage, int form, b
     return MF_OK;
 }
 
+// The next checked call's flag (call 0 when it is not to be checked).
+mf_status finite_flag(mf_plan p, bool check, hipStream_t s, mf::FiniteFlag* f) {
+    *f = mf::FiniteFlag{p->d_flag, p->h_flag, 0};
+    if (!check) return MF_OK;
+    if (++p->checked_calls == 0) {  // wrapped: the device word starts over
+        MF_HIP(mf::launch_zero_words(p->d_flag, 2, s));
+        MF_HIP(hipStreamSynchronize(s));
+        *p->h_flag = 0;
+        p->checked_calls = 1;
+    }
+    f->call = p->checked_calls;
+    return MF_OK;
+}
+
 // Lowest problem whose chain states hold a NaN or an infinity (after a
 // synchronisation of the stream), or MF_OK.
-mf_status read_finite_flag(mf_plan p, hipStream_t s) {
-    int32_t h = 0;
-    MF_HIP(hipMemcpyAsync(&h, p->d_flag, sizeof(int32_t), hipMemcpyDeviceToHost, s));
+mf_status read_finite_flag(mf_plan p, mf::FiniteFlag f, hipStream_t s) {
     MF_HIP(hipStreamSynchronize(s));
-    if (h != INT32_MAX)
-        return fail(MF_ERR_NONFINITE, "problem " + std::to_string(h) + ": a chain state holds NaN or Inf");
-    return MF_OK;
+    if (*static_cast<volatile uint32_t*>(p->h_flag) != f.call) return MF_OK;
+    unsigned long long h = 0;
+    MF_HIP(hipMemcpyAsync(&h, p->d_flag, sizeof(h), hipMemcpyDeviceToHost, s));
+    MF_HIP(hipStreamSynchronize(s));
+    return fail(MF_ERR_NONFINITE,
+                "problem " + std::to_string((int32_t)~(uint32_t)h) + ": a chain state holds NaN or Inf");
 }
 
 // Algorithm 1 for every problem (mf_sample), on the buffers of `w`.
@@ -1611,7 +1631,8 @@ mf_status sample_impl(mf_plan p, const float* d, const mf_sample_args* g, const 
         MF_HIP(mf::launch_sampler_coefs(p->d_probs, (int)p->probs.size(), d, p->d_nbar, p->d_nP, pcoef, psrc, mcoef,
                                         true, s));
     }
-    if (g->check_finite) MF_HIP(mf::launch_fill_int(p->d_flag, INT32_MAX, 1, s));
+    mf::FiniteFlag flag;
+    if (mf_status fs = finite_flag(p, g->check_finite, s, &flag); fs != MF_OK) return fs;
     // Size classes share nothing but read-only tables and the flag's minimum, and
     // one class's launches seldom fill the GPU (192 problems of four sizes, one
     // chain each: 6.68 ms one class after another, 4.20 ms side by side).  A stream
@@ -1652,14 +1673,19 @@ mf_status sample_impl(mf_plan p, const float* d, const mf_sample_args* g, const 
             a.field = pfield;
             a.packed = 1;
             if (state_out) MF_HIP(mf::launch_pack_copy_out(W, H, a, work, s));
-            if (g->check_finite) MF_HIP(mf::launch_finite_check(W, H, a, p->d_flag, s));
+            if (g->check_finite) MF_HIP(mf::launch_finite_check(W, H, a, flag, s));
             if (w.overlap) items += n_items;
             pfield += (size_t)n_items * H * W;
             continue;
         }
-        st = class_items_at(p, items, w.items_cap - (items - w.items), kv.first, pairs, false, false, s, &di, &n_items);
-        if (st != MF_OK) return st;
-        if (w.overlap) items += n_items;
+        if (form == MF_FORM_PERSISTENT && n_cool == 0) {
+            n_items = n_pids * pairs;  // the kernel finds its work items itself
+        } else {
+            st = class_items_at(p, items, w.items_cap - (items - w.items), kv.first, pairs, false, false, s, &di,
+                                &n_items);
+            if (st != MF_OK) return st;
+            if (w.overlap) items += n_items;
+        }
         const float2* cin = sin;  // the state the sampling phase starts from
         if (n_cool > 0) {
             float2* cw = (form != MF_FORM_PERSISTENT && hwork) ? hwork : work;
@@ -1674,9 +1700,11 @@ mf_status sample_impl(mf_plan p, const float* d, const mf_sample_args* g, const 
         if (form == MF_FORM_PERSISTENT) {
             mf::ResidentArgs r{};
             r.probs = p->d_probs;
-            r.items = di;
+            r.pids = p->d_class_pids + p->class_all.at(kv.first).first;
+            r.pairs = pairs;
             r.n_items = n_items;
             r.field = work;
+            r.flag = flag;
             r.state_in = cin;
             r.init_scale = g->init_scale;
             r.pcoef = pcoef;
@@ -1716,10 +1744,10 @@ mf_status sample_impl(mf_plan p, const float* d, const mf_sample_args* g, const 
         if (st != MF_OK) return st;
         // a NaN or an infinity anywhere in a chain's history reaches its final
         // state (every sweep mixes all pixels through the transforms)
-        if (g->check_finite) MF_HIP(mf::launch_finite_check(W, H, chk, p->d_flag, s));
+        if (g->check_finite && form != MF_FORM_PERSISTENT) MF_HIP(mf::launch_finite_check(W, H, chk, flag, s));
     }
     MF_HIP(cls.join());
-    return g->check_finite ? read_finite_flag(p, s) : MF_OK;
+    return g->check_finite ? read_finite_flag(p, flag, s) : MF_OK;
 }
 
 // Workspaces of mf_sample_spectrum with `pairs` chain pairs per problem.
@@ -1935,7 +1963,8 @@ mf_status mf_plan_create(mf_plan* out, int32_t n_problems, const mf_problem* pro
                         std::string(#call) + ": " + hipGetErrorString(e_));       \
         }                                                                         \
     } while (0)
-    MF_TRY(hipMalloc(&p->d_probs, n_problems * sizeof(mf::ProbDev)));
+    pd.push_back(mf::ProbDev{});  // the non-finite check's device word, zero
+    MF_TRY(hipMalloc(&p->d_probs, pd.size() * sizeof(mf::ProbDev)));
     MF_TRY(hipMalloc(&p->d_nbar, off * sizeof(float)));
     MF_TRY(hipMalloc(&p->d_nP, off * sizeof(float)));
     MF_TRY(hipMalloc(&p->d_nPt, off / 2 * sizeof(float2)));
@@ -1946,7 +1975,9 @@ mf_status mf_plan_create(mf_plan* out, int32_t n_problems, const mf_problem* pro
     MF_TRY(hipMalloc(&p->d_band_scale, std::max(bands, 1) * sizeof(double)));
     MF_TRY(hipMalloc(&p->d_band_amps, std::max(bands, 1) * sizeof(double)));
     MF_TRY(hipMalloc(&p->d_band_modes, std::max(bands, 1) * sizeof(int32_t)));
-    MF_TRY(hipMalloc(&p->d_flag, sizeof(int32_t)));
+    p->d_flag = reinterpret_cast<unsigned long long*>(p->d_probs + n_problems);
+    MF_TRY(hipHostMalloc(&p->h_flag, sizeof(uint32_t), hipHostMallocCoherent));
+    *p->h_flag = 0;
     {
         // problem ids per size class: all of them, then the band-spectrum ones
         std::vector<int32_t> ids;
@@ -1963,7 +1994,7 @@ mf_status mf_plan_create(mf_plan* out, int32_t n_problems, const mf_problem* pro
         MF_TRY(hipMalloc(&p->d_class_pids, ids.size() * sizeof(int32_t)));
         MF_TRY(hipMemcpy(p->d_class_pids, ids.data(), ids.size() * sizeof(int32_t), hipMemcpyHostToDevice));
     }
-    MF_TRY(hipMemcpy(p->d_probs, pd.data(), n_problems * sizeof(mf::ProbDev), hipMemcpyHostToDevice));
+    MF_TRY(hipMemcpy(p->d_probs, pd.data(), pd.size() * sizeof(mf::ProbDev), hipMemcpyHostToDevice));
     MF_TRY(hipMemcpy(p->d_nbar, p->host_nbar.data(), off * sizeof(float), hipMemcpyHostToDevice));
     MF_TRY(hipMemcpy(p->d_band_base, bb.data(), n_problems * sizeof(int32_t), hipMemcpyHostToDevice));
     MF_TRY(hipMemcpy(p->d_band_count, bc.data(), n_problems * sizeof(int32_t), hipMemcpyHostToDevice));
@@ -2448,7 +2479,8 @@ mf_status mf_sample_spectrum(mf_plan p, const float* d, const mf_spectrum_args* 
     float2* psrc = reinterpret_cast<float2*>(pcoef + half);
     float4* mcoef = reinterpret_cast<float4*>(psrc + half);
     MF_HIP(mf::launch_sampler_coefs(p->d_probs, (int)p->probs.size(), d, p->d_nbar, p->d_nP, pcoef, psrc, mcoef, false, s));
-    if (g->check_finite) MF_HIP(mf::launch_fill_int(p->d_flag, INT32_MAX, 1, s));
+    mf::FiniteFlag flag;
+    if (mf_status fs = finite_flag(p, g->check_finite, s, &flag); fs != MF_OK) return fs;
     for (auto& kv : p->classes) {
         const int H = kv.first.first, W = kv.first.second;
         mf::ItemDev* di = nullptr;
@@ -2503,10 +2535,10 @@ mf_status mf_sample_spectrum(mf_plan p, const float* d, const mf_spectrum_args* 
             chk.items = di;
             chk.n_items = n_items;
             chk.field = work;
-            MF_HIP(mf::launch_finite_check(W, H, chk, p->d_flag, s));
+            MF_HIP(mf::launch_finite_check(W, H, chk, flag, s));
         }
     }
-    return g->check_finite ? read_finite_flag(p, s) : MF_OK;
+    return g->check_finite ? read_finite_flag(p, flag, s) : MF_OK;
 }
 
 }  // extern "C"

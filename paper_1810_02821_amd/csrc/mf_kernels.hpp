@@ -26,6 +26,20 @@ struct ItemDev {
     int32_t pid;        // = probs[prob].pid
 };
 
+// Where a call's kernels report a chain state with a NaN or an infinity.  Calls
+// are numbered, so that nothing is cleared between them: *first holds the
+// largest (call << 32 | ~problem), hence the newest call's lowest problem, and
+// *seen, in host memory, the number of the last call that reported at all.
+struct FiniteFlag {
+    unsigned long long* first;
+    uint32_t* seen;
+    uint32_t call;  // 0: do not check
+};
+__device__ inline void report_non_finite(const FiniteFlag& f, int prob) {
+    atomicMax(f.first, (unsigned long long)f.call << 32 | ~(uint32_t)prob);
+    *static_cast<volatile uint32_t*>(f.seen) = f.call;
+}
+
 // Cooling levels carried by value in the kernel arguments of the persistent
 // kernels (no device table to upload), so that a call that launches them can
 // be captured into a caller's graph.  Longer schedules run in several launches.
@@ -163,8 +177,7 @@ hipError_t launch_col_pack(int W, int H, const SweepArgs& a, hipStream_t s);
 hipError_t launch_zero_words(void* p, int64_t n_words, hipStream_t s);
 // flag[0] = min(flag[0], problem) for every item whose field (H x W elements
 // of the given storage) holds a NaN or an infinity.
-hipError_t launch_finite_check(int W, int H, const SweepArgs& a, int32_t* flag, hipStream_t s);
-hipError_t launch_fill_int(int32_t* p, int32_t v, int64_t n, hipStream_t s);
+hipError_t launch_finite_check(int W, int H, const SweepArgs& a, FiniteFlag flag, hipStream_t s);
 // Loss terms of a band-spectrum problem at s (one item per problem, d and s
 // concatenated, d already divided by the response): per item FP64 partial
 // sums of N_eff^-1 (d - s)^2 and (s - s_true)^2 into part[item][block][2],

@@ -10,7 +10,8 @@ namespace mf {
 
 struct ResidentArgs {
     const ProbDev* probs;
-    const ItemDev* items;
+    const int32_t* pids;      // problems of the class; item i is pair i % pairs of problem pids[i / pairs]
+    int32_t pairs;
     int32_t n_items;
     float2* field;            // final pair states [item] (pixel space)
     const float2* state_in;   // start states or null
@@ -24,6 +25,7 @@ struct ResidentArgs {
     int32_t burn_in, n_samples, thin;
     float* samples;           // [problem][chain][sample][H][W] or null
     int32_t chains;
+    FiniteFlag flag;          // final states' check
 };
 
 // Deterministic messenger solve (Wiener filter / adjoint) of one problem per

@@ -1326,11 +1326,6 @@ __global__ void zero_words_kernel(uint32_t* p, int64_t n) {
         p[e] = 0u;
 }
 
-__global__ void fill_int_kernel(int32_t* p, int32_t v, int64_t n) {
-    for (int64_t e = (int64_t)blockIdx.x * blockDim.x + threadIdx.x; e < n; e += (int64_t)gridDim.x * blockDim.x)
-        p[e] = v;
-}
-
 __global__ void band_dof_kernel(const int32_t* modes, int32_t prior_dof, int32_t* dof, int n) {
     for (int b = blockIdx.x * blockDim.x + threadIdx.x; b < n; b += gridDim.x * blockDim.x)
         dof[b] = max(0, modes[b] + prior_dof);
@@ -1346,7 +1341,7 @@ __global__ void add_kernel(const float* x, float* y, int64_t n) {
 // problem `prob`, the imaginary part to `pair`).
 // Each item's field is scanned by `per` consecutive blocks (enough blocks over
 // all items to keep every CU streaming).
-__global__ void finite_check_kernel(SweepArgs a, int64_t n, int32_t per, int32_t* flag) {
+__global__ void finite_check_kernel(SweepArgs a, int64_t n, int32_t per, FiniteFlag flag) {
     const ItemDev it = a.items[blockIdx.x / per];
     const int64_t b0 = blockIdx.x % per;
     bool bad_a = false, bad_b = false;
@@ -1362,8 +1357,8 @@ __global__ void finite_check_kernel(SweepArgs a, int64_t n, int32_t per, int32_t
     if (!a.packed) bad_a |= bad_b;
     const bool any_a = __syncthreads_or(bad_a), any_b = __syncthreads_or(bad_b);
     if (threadIdx.x == 0) {
-        if (any_a) atomicMin(flag, it.prob);
-        if (a.packed && any_b && it.pair >= 0) atomicMin(flag, it.pair);
+        if (any_a) report_non_finite(flag, it.prob);
+        if (a.packed && any_b && it.pair >= 0) report_non_finite(flag, it.pair);
     }
 }
 
@@ -1743,11 +1738,6 @@ hipError_t launch_zero_words(void* p, int64_t n_words, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_fill_int(int32_t* p, int32_t v, int64_t n, hipStream_t s) {
-    hipLaunchKernelGGL(fill_int_kernel, elementwise_grid(n), dim3(256), 0, s, p, v, n);
-    return hipGetLastError();
-}
-
 hipError_t launch_band_dof(const int32_t* modes, int32_t prior_dof, int32_t* dof, int n, hipStream_t s) {
     if (n <= 0) return hipSuccess;
     hipLaunchKernelGGL(band_dof_kernel, elementwise_grid(n), dim3(256), 0, s, modes, prior_dof, dof, n);
@@ -1759,7 +1749,7 @@ hipError_t launch_add(const float* x, float* y, int64_t n, hipStream_t s) {
     return hipGetLastError();
 }
 
-hipError_t launch_finite_check(int W, int H, const SweepArgs& a, int32_t* flag, hipStream_t s) {
+hipError_t launch_finite_check(int W, int H, const SweepArgs& a, FiniteFlag flag, hipStream_t s) {
     if (a.n_items <= 0) return hipSuccess;
     const int64_t n = (int64_t)H * W;
     int64_t per = (2048 + a.n_items - 1) / a.n_items;  // about 2048 blocks in all
