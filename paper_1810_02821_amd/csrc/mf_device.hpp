@@ -305,19 +305,23 @@ __device__ __forceinline__ void group_stages(float2 (&v)[P], unsigned k1, const 
         group_stages<L, NS, P, Q * R, INV>(v, k1, tw);
     }
 }
-// Product of the passes from NS points on that one thread takes together: as
-// many as keep it within 18 elements.
+// Product of the passes from NS points on that one thread takes together: the
+// next one and as many more as keep it within 12 elements.  (Up to 18 saves 162
+// points an exchange but leaves 9 threads of 32 at work: column kernel of 162
+// rows 13.6 us against 12.2, row kernel of 162 points 14.4 against 13.2; at most
+// 9 splits 4 3 and costs 192 and 972 points 3%.)
 template <int L, int NS>
 constexpr int group_size() {
-    int P = 1;
-    while (NS * P < L && P * radix_of(L / (NS * P)) <= 18) P *= radix_of(L / (NS * P));
+    int P = radix_of(L / NS);
+    while (NS * P < L && P * radix_of(L / (NS * P)) <= 12) P *= radix_of(L / (NS * P));
     return P;
 }
 // Passes of a length that is not a power of two, P elements per thread and
-// exchange (162 = (2 3 3) (3 3): two exchanges instead of five).  These kernels
-// are bound by the chain of exchanges and barriers rather than by arithmetic:
-// column kernels of 162, 972 and 1458 rows 18.1 -> 15.0, 103 -> 80 and 297 ->
-// 255 us, row kernel of 1944 points 205 -> 163 us.
+// exchange (162 = (2 3) (3 3) 3: three exchanges instead of five, 972 = (4 3)
+// (3 3) (3 3): three instead of six).  These kernels are bound by the chain of
+// exchanges and barriers rather than by arithmetic: column kernels of 162 rows
+// x 32 fields 18.1 -> 12.2 us and of 972 rows 103 -> 53 us with their narrower
+// tiles, row kernel of 1944 points 205 -> 169 us.
 template <int L, int P, int NS, int TPG, bool INV, typename TW>
 __device__ __forceinline__ void group_pass(float2* buf, unsigned lane, const TW& tw) {
     constexpr int NT = L / P;

@@ -629,10 +629,10 @@ void row_kernel_f(SweepArgs a, int H) {
 // autotuner may pick another feasible (TC, NTH).
 // Default tile of a column length (16 columns, 8 from 1025 rows so that the
 // tile fits in LDS) and its threads.  Lengths with a factor 3, whose threads
-// hold up to 18 elements, take narrower tiles, of which more fit in a CU (us
+// hold up to 12 elements, take narrower tiles, of which more fit in a CU (us
 // per launch, 16 columns of 256, 512 threads / these: 32 fields of 162 x 192
-// 15.0 / 13.6, 8 of 972 x 648 80 / 53; 8 of 1458 x 1944, 8 columns of 1024
-// threads / these 255 / 230).
+// 15.7 / 12.2, 8 of 972 x 648 81 / 53; 8 of 1458 x 1944, 8 columns of 1024
+// threads / these 261 / 233).
 constexpr int col_tc_of(int L) { return is_pow2(L) ? (L > 1024 ? 8 : 16) : L > 1024 ? 4 : 8; }
 constexpr int col_nth_of(int L) {
     return is_pow2(L) ? (L >= 1024 ? 1024 : (L >= 512 ? 512 : 256)) : L > 512 ? 512 : L > 128 ? 256 : 128;
