@@ -10,6 +10,7 @@
 #include <cstring>
 #include <array>
 #include <map>
+#include <mutex>
 #include <string>
 #include <vector>
 
@@ -63,6 +64,45 @@ struct HostProblem {
     std::vector<int32_t> band_modes;  // modes per band (band spectra)
     double amp = 1, k0 = 1, n = 2;
 };
+
+// Pinned host words for the plans' non-finite checks, from one page that the
+// process keeps (a pinned allocation of its own would cost each plan 20 us and
+// its destruction 27).  A plan takes a word and gives it back; when all are out
+// it allocates its own.
+class FlagWords {
+    static constexpr int kWords = 1024;
+    std::mutex m;
+    uint32_t* page = nullptr;
+    std::vector<uint32_t*> idle;
+
+public:
+    hipError_t take(uint32_t** out) {
+        constexpr unsigned how = hipHostMallocPortable | hipHostMallocMapped | hipHostMallocCoherent;
+        std::lock_guard<std::mutex> lock(m);
+        if (!page) {
+            const hipError_t e = hipHostMalloc(&page, kWords * sizeof(uint32_t), how);
+            if (e != hipSuccess) {
+                page = nullptr;
+                return e;
+            }
+            idle.reserve(kWords);
+            for (int i = kWords - 1; i >= 0; --i) idle.push_back(page + i);
+        }
+        if (idle.empty()) return hipHostMalloc(out, sizeof(uint32_t), how);
+        *out = idle.back();
+        idle.pop_back();
+        return hipSuccess;
+    }
+    void give(uint32_t* w) {
+        std::lock_guard<std::mutex> lock(m);
+        if (page && w >= page && w < page + kWords) idle.push_back(w);
+        else (void)hipHostFree(w);
+    }
+};
+FlagWords& flag_words() {
+    static FlagWords* w = new FlagWords;  // outlives every plan
+    return *w;
+}
 
 // A device buffer that grows on demand and is freed with the plan.
 struct DevBuf {
@@ -162,7 +202,7 @@ struct mf_plan_s {
         (void)hipFree(d_class_pids);
         (void)hipFree(d_band_modes);
         (void)hipFree(d_band_amps);
-        if (h_flag) (void)hipHostFree(h_flag);
+        if (h_flag) flag_words().give(h_flag);
         dprime.release();
         lossbuf.release();
         for (auto& kv : d_tw) (void)hipFree(kv.second);
@@ -1976,7 +2016,7 @@ mf_status mf_plan_create(mf_plan* out, int32_t n_problems, const mf_problem* pro
     MF_TRY(hipMalloc(&p->d_band_amps, std::max(bands, 1) * sizeof(double)));
     MF_TRY(hipMalloc(&p->d_band_modes, std::max(bands, 1) * sizeof(int32_t)));
     p->d_flag = reinterpret_cast<unsigned long long*>(p->d_probs + n_problems);
-    MF_TRY(hipHostMalloc(&p->h_flag, sizeof(uint32_t), hipHostMallocCoherent));
+    MF_TRY(flag_words().take(&p->h_flag));
     *p->h_flag = 0;
     {
         // problem ids per size class: all of them, then the band-spectrum ones
