@@ -388,18 +388,6 @@ __device__ __forceinline__ float swap_lanes(float v) {
 }
 
 // ------------------------------------------------------- real-field filter --
-// p / (p + T) to FP32 rounding: one Newton step on the reciprocal and one
-// correction with the exact remainder, the rounding of p + T included.
-__device__ __forceinline__ float wiener_f(float p, float T) {
-    const float den = p + T;
-    const float big = fmaxf(p, T), small = fminf(p, T);
-    const float lo = small - (den - big);  // p + T = den + lo exactly
-    float r = __builtin_amdgcn_rcpf(den);
-    r = fmaf(fmaf(-den, r, 1.0f), r, r);
-    const float q = p * r;
-    return fmaf(fmaf(-lo, q, fmaf(-den, q, p)), r, q);
-}
-
 // A real field folded to half a complex field z = t_even + i t_odd (alternate
 // rows or columns): with f(k), f(k + M) the filter at the two modes that share
 // one of the folded transform's, th the twiddle (cos, -sin) of the fold and
@@ -409,9 +397,19 @@ __device__ __forceinline__ float wiener_f(float p, float T) {
 struct RealFilter {
     float a, m, b;
 };
+// In FP64 up to the last rounding: a solve repeats the coefficients' errors on
+// every sweep, and three FP32 roundings each show in its slowest modes.  (FP64
+// issues at FP32's rate here; the reciprocal takes two Newton steps.)
 __device__ __forceinline__ RealFilter real_filter(float p0, float p1, float T, float2 th, float scale) {
-    const float f0 = wiener_f(p0, T), f1 = wiener_f(p1, T), lo = 1.0f + th.y, hi = 1.0f - th.y;
-    return {fmaf(f0, lo, f1 * hi) * scale, fmaf(f0, hi, f1 * lo) * scale, (f0 - f1) * th.x * scale};
+    const auto f = [&](float p) {
+        const double den = (double)p + (double)T;
+        double r = __builtin_amdgcn_rcp(den);
+        r = fma(fma(-den, r, 1.0), r, r);
+        r = fma(fma(-den, r, 1.0), r, r);
+        return (double)p * r;
+    };
+    const double f0 = f(p0), f1 = f(p1), sum = (f0 + f1) * scale, dif = (f0 - f1) * scale;
+    return {(float)fma((double)th.y, dif, sum), (float)fma(-(double)th.y, dif, sum), (float)(dif * th.x)};
 }
 
 // -------------------------------------------------------- normal variates --
