@@ -49,7 +49,7 @@ struct ShearStreamArgs {
     const float2* nPt;        // column-pair copy: [pix_off/2 + (kx/2) H + ky] = (nP(ky,kx), nP(ky,kx+1))
     float b_ratio;
     const float2* tw_row;     // pass tables of W (pass_plan)
-    const float2* tw_col;     // pass tables of H (pass_plan)
+    const float2* tw_col;     // pass tables of H (pass_plan), W_H^r 2 H entries before them
     uint32_t key0, key1;
     uint32_t sweep;           // global sweep index
     float lambda;             // cooling level: T = lambda * tau

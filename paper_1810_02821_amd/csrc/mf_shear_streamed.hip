@@ -336,7 +336,11 @@ __global__ __launch_bounds__(ShearColShape<L>::NTH) void shear_col_kernel(ShearS
     // padded exchange layouts from 256 rows (the HBM-side passes) where they
     // keep the resident workgroups per CU, else the XOR swizzle; an emission
     // sweep's round trip starts and ends in the natural-order layout AN
-    constexpr int kExtra = 8 * lds_tw_len<L>();  // the twiddles beside the tile
+    // up to 512 rows the table W_L^r (2 L entries before the pass tables), half the
+    // pass tables' size (32 fields of 512^2 47.9 against 49.3 us per launch)
+    constexpr bool kBase = L <= 512;
+    constexpr int kTw = L < 256 ? 1 : kBase ? L : lds_tw_len<L>();
+    constexpr int kExtra = 8 * (L < 256 ? L : kTw);  // the twiddles beside the tile
     constexpr bool kPad = L >= 256 && lds_keeps_blocks(TC * ShearColShape<L>::SEG * 8 + kExtra,
                                                        TC * PairLayout<L, TC>::SEG * 8 + kExtra);
     constexpr int A1 = kPad ? PairLayout<L, TC>::A1 : -1, AN = kPad ? PairLayout<L, TC>::AN : -1;
@@ -345,8 +349,11 @@ __global__ __launch_bounds__(ShearColShape<L>::NTH) void shear_col_kernel(ShearS
     constexpr int H = L;
     constexpr int half = TC / 2;
     __shared__ float2 lds[TC * SEG];
-    __shared__ float2 twl[L >= 256 ? lds_tw_len<L>() : 1];  // twiddles of the HBM-side passes
-    const TwSplit<lds_tw_lim(L)> tws{a.tw_col, twl};
+    __shared__ float2 twl[kTw];  // twiddles of the HBM-side passes
+    const auto tws = [&] {
+        if constexpr (kBase) return TwBase{twl};
+        else return TwSplit<lds_tw_lim(L)>{a.tw_col, twl};
+    }();
     const unsigned tid = threadIdx.x;
     // tile fastest: an XCD runs neighbouring tiles of one item together
     const int64_t t = xcd_block(blockIdx.x, gridDim.x);
@@ -360,7 +367,9 @@ __global__ __launch_bounds__(ShearColShape<L>::NTH) void shear_col_kernel(ShearS
     const unsigned cid = tid / TPC, lane = tid % TPC;
     if constexpr (L >= 256) {
         // first forward pass straight from HBM (plan of mf_streamed_fft.hpp)
-        stage_twiddles<L, NTH>(twl, a.tw_col, tid);
+        if constexpr (kBase)
+            for (unsigned i = tid; i < (unsigned)L; i += NTH) twl[i] = (a.tw_col - 2 * L)[i];
+        else stage_twiddles<L, NTH>(twl, a.tw_col, tid);
         col_first_forward<L, TC, NTH, SEG, A1>(lds, fin, W, tid, col_of);
         __syncthreads();
         col_forward_rest<L, TPC, A1>(lds + cid * SEG, lane, tws);
