@@ -49,14 +49,22 @@ struct Filt {
     float fp, fm, wp, wm;
 };
 
-// (f_+, f_-, w_+, w_-) of one mode off k = 0, the 1/n of the inverse transform
-// and the normals' sqrt(2 ln 2) folded in: with h = f / 2n, w / 2n = sqrt(h T / 2).
+// (f_+, f_-, w_+, w_-) of one mode, the 1/n of the inverse transform and the
+// normals' sqrt(2 ln 2) folded in: with h = f / 2n, w / 2n = sqrt(h T / 2).
 __device__ __forceinline__ Filt filt(float nP, float r, float T, float n) {
     const float c = 0.5f / n, g = 0.5f * kBoxMuller2 * T;
     const float hE = nP * c * __builtin_amdgcn_rcpf(nP + T);
     const float hB = nP * (r * c) * __builtin_amdgcn_rcpf(fmaf(r, nP, T));
     const float wE = __builtin_amdgcn_sqrtf(hE * g), wB = __builtin_amdgcn_sqrtf(hB * g);
     return {hE + hB, hE - hB, wE + wB, wE - wB};
+}
+// The same at k = 0, which has no data: f = 0 and the prior w = sqrt(n nP).  Not
+// filt at a T taken to infinity: its h falls below the normal numbers there.
+template <int N>
+__device__ __forceinline__ Filt prior_filt(float nP, float r) {
+    constexpr float c = 0.5f / (float)N;
+    const float wE = c * __builtin_amdgcn_sqrtf(kBoxMuller2 * nP), wB = c * __builtin_amdgcn_sqrtf(kBoxMuller2 * (r * nP));
+    return {0.f, 0.f, wE + wB, wE - wB};
 }
 // The Fourier step kappa^(k) = f_+ u(k) + f_- conj(u(-k)) + w_+ eta(k) + w_- conj(eta(-k)),
 // u = conj(D) Z, times D unless the sweep emits kappa.  eta: the mode variates
@@ -101,11 +109,8 @@ struct ShearStep {
         sb = mode(c, um, u, em, e, dm);
     }
     __device__ __forceinline__ float2 single(unsigned ky, unsigned kx, float2 z, float2 zm) const {
-        const bool k0 = ky == 0 && kx == 0;
-        // at k = 0 (no data) f = 0, and the messenger variance taken to infinity leaves the prior w
-        Filt c = filt(nP[ky * N + kx], r, k0 ? 1e20f : T, (float)(N * N));
-        c.fp = k0 ? 0.f : c.fp;
-        c.fm = k0 ? 0.f : c.fm;
+        const float np = nP[ky * N + kx];
+        const Filt c = ky == 0 && kx == 0 ? prior_filt<N>(np, r) : filt(np, r, T, (float)(N * N));
         const float2 d = ks<N>(ky, kx);
         const bool flip = (ky == (unsigned)(N / 2)) != (kx == (unsigned)(N / 2));
         float2 e = make_float2(0.f, 0.f), em = e;

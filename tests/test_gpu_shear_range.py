@@ -1,0 +1,35 @@
+"""Mass-mapping samples at the ends of the accepted scales, in both forms, on
+the oracle's random stream: a signal far below the noise, whose k = 0 (no data)
+is a draw from a prior of 1e-24 or 1e-30."""
+import types
+
+import numpy as np
+import pytest
+
+from gpu_common import REL_TOL, banner, rel
+from oracle import shear as osh
+from paper_1810_02821_amd import synth
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("H,W", [(32, 32), (128, 128), (32, 64)])
+@pytest.mark.parametrize("signal,units", [(1e-24, 1.0), (1e-30, 1.0)])
+def test_samples_far_from_unit_scale_match_oracle(H, W, signal, units):
+    import paper_1810_02821_amd as mf
+    banner(f"shear samples {H}x{W} signal {signal} units {units}")
+    b_ratio = 0.3
+    prob = synth.config_shear(5, H, b_ratio, width=W)
+    prob.spectrum = types.SimpleNamespace(kind="powerlaw", amp=signal * units, k0=1.0, n=2.0)
+    prob.noise_var = prob.noise_var * units
+    prob.gamma = prob.gamma * np.sqrt(units)
+    plan = mf.Plan([prob])
+    out, _ = plan.shear_sample(plan.concat_complex([prob.gamma]), 17, 1, 1, 2, 1, b_ratio=b_ratio)
+    got = out.view(2, H, W).cpu().numpy().astype(np.complex128)
+    ref, _ = osh.sample_shear_chain(prob, 17, 0, 0, 1, 2, 1, b_ratio)
+    scale = np.sqrt(signal * units)  # away from the smallest doubles' squares
+    for k in range(2):
+        assert rel(got[k] / scale, ref[k] / scale) < REL_TOL
+        mean, want = got[k].mean() / scale, ref[k].mean() / scale  # the k = 0 draw
+        assert abs(mean - want) < REL_TOL * abs(want)
+    plan.close()
