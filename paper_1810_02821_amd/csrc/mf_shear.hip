@@ -50,16 +50,21 @@ struct Filt {
 };
 
 // (f_+, f_-, w_+, w_-) of one mode, the 1/n of the inverse transform and the
-// normals' sqrt(2 ln 2) folded in: with h = f / 2n, w / 2n = sqrt(h T / 2).
-__device__ __forceinline__ Filt filt(float nP, float r, float T, float n) {
-    const float c = 0.5f / n, g = 0.5f * kBoxMuller2 * T;
-    const float hE = nP * c * __builtin_amdgcn_rcpf(nP + T);
-    const float hB = nP * (r * c) * __builtin_amdgcn_rcpf(fmaf(r, nP, T));
-    const float wE = __builtin_amdgcn_sqrtf(hE * g), wB = __builtin_amdgcn_sqrtf(hB * g);
-    return {hE + hB, hE - hB, wE + wB, wE - wB};
+// normals' sqrt(2 ln 2) folded in: f / 2n, and w / 2n = sqrt(nP T / (nP + T)) / 2N.
+// Scaled only after the ratios nP / (nP + T) and T / (nP + T) are formed, and by
+// N = sqrt(n) outside the root: with 1/n on nP or T first, variances below 1e-33
+// leave the normal numbers (which the root takes as zero).
+template <int N>
+__device__ __forceinline__ Filt filt(float nP, float r, float T) {
+    constexpr float c = 0.5f / (float)(N * N), cw = 0.5f / (float)N;
+    const float nB = r * nP, g = kBoxMuller2 * T;
+    const float rE = __builtin_amdgcn_rcpf(nP + T), rB = __builtin_amdgcn_rcpf(nB + T);
+    const float fE = nP * rE, hB = c * (nB * rB);
+    const float wE = __builtin_amdgcn_sqrtf(nP * (g * rE)), vB = cw * __builtin_amdgcn_sqrtf(nB * (g * rB));
+    return {fmaf(c, fE, hB), fmaf(c, fE, -hB), fmaf(cw, wE, vB), fmaf(cw, wE, -vB)};
 }
 // The same at k = 0, which has no data: f = 0 and the prior w = sqrt(n nP).  Not
-// filt at a T taken to infinity: its h falls below the normal numbers there.
+// filt at a large stand-in for T, which is exact only for nP far below it.
 template <int N>
 __device__ __forceinline__ Filt prior_filt(float nP, float r) {
     constexpr float c = 0.5f / (float)N;
@@ -92,7 +97,7 @@ struct ShearStep {
     }
     __device__ __forceinline__ void pair(int k2, unsigned ky, unsigned kx, float2 za, float2 zb, float2& sa,
                                          float2& sb) const {
-        const Filt c = filt(nP[ky * N + kx], r, T, (float)(N * N));
+        const Filt c = filt<N>(nP[ky * N + kx], r, T);
         // ky = k1 + RC k2 is below the Nyquist row exactly for k2 < RD/2
         const float y = y1 + (float)(S::RC * k2 - (k2 >= S::RD / 2 ? N : 0));
         const float q = __builtin_amdgcn_rcpf(fmaf(y, y, x2));  // k = 0 mirrors itself: never here
@@ -110,7 +115,7 @@ struct ShearStep {
     }
     __device__ __forceinline__ float2 single(unsigned ky, unsigned kx, float2 z, float2 zm) const {
         const float np = nP[ky * N + kx];
-        const Filt c = ky == 0 && kx == 0 ? prior_filt<N>(np, r) : filt(np, r, T, (float)(N * N));
+        const Filt c = ky == 0 && kx == 0 ? prior_filt<N>(np, r) : filt<N>(np, r, T);
         const float2 d = ks<N>(ky, kx);
         const bool flip = (ky == (unsigned)(N / 2)) != (kx == (unsigned)(N / 2));
         float2 e = make_float2(0.f, 0.f), em = e;
@@ -184,6 +189,7 @@ __global__ __launch_bounds__(SquareShape<N>::type::NT, 4) void resident_shear_ke
     int64_t k = 0;
     for (int lv = 0; lv < a.lv.n; ++lv) {
         const float T = (float)(a.lv.lambda[lv] * (double)pr.tau);
+        const float sdT = kBoxMuller * __builtin_amdgcn_sqrtf(T);  // apart from sqrt(1 - a): T (1 - a) may be subnormal
         for (int s = 0; s < a.lv.sweeps[lv]; ++s, ++k) {
             const uint32_t sweep = a.sweep0 + (uint32_t)k;
             const float2* tw = twl + per_sweep_zero();
@@ -209,8 +215,8 @@ __global__ __launch_bounds__(SquareShape<N>::type::NT, 4) void resident_shear_ke
                     if (a.stochastic) {
                         const Polar2 z = pair_polar(e2, sweep, (uint32_t)pr.pid, kStagePixel, (uint32_t)it.pair,
                                                     a.key0, a.key1);
-                        const float r0 = z.a.r * __builtin_amdgcn_sqrtf(fmaxf(kBoxMuller2 * T * (1.f - a0), 0.f));
-                        const float r1 = z.b.r * __builtin_amdgcn_sqrtf(fmaxf(kBoxMuller2 * T * (1.f - a1), 0.f));
+                        const float r0 = z.a.r * (sdT * __builtin_amdgcn_sqrtf(fmaxf(1.f - a0, 0.f)));
+                        const float r1 = z.b.r * (sdT * __builtin_amdgcn_sqrtf(fmaxf(1.f - a1, 0.f)));
                         s0 = make_float2(fmaf(r0, z.a.c, s0.x), fmaf(r0, z.a.s, s0.y));
                         s1 = make_float2(fmaf(r1, z.b.c, s1.x), fmaf(r1, z.b.s, s1.y));
                     }

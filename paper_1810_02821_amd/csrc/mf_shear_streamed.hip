@@ -158,6 +158,7 @@ __global__ __launch_bounds__(kRowThreads) void shear_row_kernel(ShearStreamArgs 
     }
     // pixel step in shear space: t = (1 - a) s + a gamma (+ sqrt(T (1 - a)) xi)
     const float T = a.lambda * pr.tau;
+    const float sdT = __builtin_amdgcn_sqrtf(T);  // apart from sqrt(1 - a): T (1 - a) may be subnormal
     for (unsigned pp = lane; pp < (unsigned)L / 2; pp += TPR) {
         const unsigned x = 2 * pp;
         const int64_t px = pr.pix_off + (int64_t)y * W + x;
@@ -172,8 +173,8 @@ __global__ __launch_bounds__(kRowThreads) void shear_row_kernel(ShearStreamArgs 
         if (a.stochastic && valid) {
             const uint32_t j2 = (uint32_t)(((int64_t)y * W + x) >> 1);
             const Normals2 z = pair_normals(j2, a.sweep, (uint32_t)pr.pid, kStagePixel, (uint32_t)it.pair, a.key0, a.key1);
-            const float sg0 = __builtin_amdgcn_sqrtf(fmaxf(T * (1.f - a0), 0.f));
-            const float sg1 = __builtin_amdgcn_sqrtf(fmaxf(T * (1.f - a1), 0.f));
+            const float sg0 = sdT * __builtin_amdgcn_sqrtf(fmaxf(1.f - a0, 0.f));
+            const float sg1 = sdT * __builtin_amdgcn_sqrtf(fmaxf(1.f - a1, 0.f));
             s0 = make_float2(fmaf(sg0, z.a.x, s0.x), fmaf(sg0, z.a.y, s0.y));
             s1 = make_float2(fmaf(sg1, z.b.x, s1.x), fmaf(sg1, z.b.y, s1.y));
         }
@@ -251,6 +252,7 @@ __global__ __launch_bounds__(kRowThreads) void shear_row_kernel_f(ShearStreamArg
     // first forward pass
     {
         const float T = a.lambda * pr.tau;
+        const float sdT = __builtin_amdgcn_sqrtf(T);  // apart from sqrt(1 - a): T (1 - a) may be subnormal
         const bool odd = lane & 1u;
         float2 v[ITL][RL];
 #pragma unroll
@@ -291,7 +293,7 @@ __global__ __launch_bounds__(kRowThreads) void shear_row_kernel_f(ShearStreamArg
                 const float2 g0 = a0 > 0.f ? make_float2(a0 * g.x, a0 * g.y) : make_float2(0.f, 0.f);
                 float2 s0 = make_float2(fmaf(1.f - a0, v[i][r].x, g0.x), fmaf(1.f - a0, v[i][r].y, g0.y));
                 if (a.stochastic && valid) {
-                    const float sg0 = __builtin_amdgcn_sqrtf(fmaxf(T * (1.f - a0), 0.f));
+                    const float sg0 = sdT * __builtin_amdgcn_sqrtf(fmaxf(1.f - a0, 0.f));
                     s0 = make_float2(fmaf(sg0, z[r].x, s0.x), fmaf(sg0, z[r].y, s0.y));
                 }
                 v[i][r] = s0;

@@ -1,6 +1,7 @@
 """Mass-mapping samples at the ends of the accepted scales, in both forms, on
 the oracle's random stream: a signal far below the noise, whose k = 0 (no data)
-is a draw from a prior of 1e-24 or 1e-30."""
+is a draw from a prior of 1e-24 or 1e-30, and everything in units that make the
+variances about 1e-36, still normal FP32 numbers."""
 import types
 
 import numpy as np
@@ -14,7 +15,7 @@ pytestmark = pytest.mark.gpu
 
 
 @pytest.mark.parametrize("H,W", [(32, 32), (128, 128), (32, 64)])
-@pytest.mark.parametrize("signal,units", [(1e-24, 1.0), (1e-30, 1.0)])
+@pytest.mark.parametrize("signal,units", [(1e-24, 1.0), (1e-30, 1.0), (1.0, 1e-35)])
 def test_samples_far_from_unit_scale_match_oracle(H, W, signal, units):
     import paper_1810_02821_amd as mf
     banner(f"shear samples {H}x{W} signal {signal} units {units}")
