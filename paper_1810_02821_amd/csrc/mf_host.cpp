@@ -1334,7 +1334,9 @@ mf_status spectrum_streamed(mf_plan p, const mf::ItemDev* di, int n_items, int H
 // streamed size class on a scratch field and keep the fastest of each (all
 // shapes do the same arithmetic, element for element).  Choices can be
 // persisted in the file named by MF_TUNE_CACHE: lines "gfx950 H W tc nth"
-// (column tiles) and "gfx950-rows H W rows" (rows per fused row block).
+// (column tiles), "gfx950-rows H W rows" (rows per fused row block) and
+// "gfx950-narrow H W tc nth rows" (both, for launches too small to fill the
+// GPU).  The last line of a class and kind counts.
 mf_status autotune(mf_plan p) {
     const char* cache_path = std::getenv("MF_TUNE_CACHE");
     std::map<std::pair<int, int>, std::pair<int, int>> cached;
@@ -1373,11 +1375,24 @@ mf_status autotune(mf_plan p) {
         const int H = kv.first.first, W = kv.first.second;
         if (H < 256 && W < 256) continue;  // small classes run on the persistent kernel or are launch-bound
         int tc[8], nth[8], rows[8];
-        const int nc = H >= 256 ? mf::col_shape_candidates(H, tc, nth, 8) : 0;
+        const int n_tiles = mf::col_shape_candidates(H, tc, nth, 8);
+        const int nc = H >= 256 ? n_tiles : 0;
         const int nr = mf::fused_row_candidates(W, rows, 8);
+        // a shape of the file counts only if it is built (the file may be of another version)
+        auto tile_built = [&](int t, int n) {
+            for (int i = 0; i < n_tiles; ++i)
+                if (tc[i] == t && nth[i] == n) return true;
+            return false;
+        };
+        auto rows_built = [&](int r) { return std::find(rows, rows + nr, r) != rows + nr; };
         auto cc = cached.find({H, W});
         auto cr = cached_rows.find({H, W});
         auto cn = cached_narrow.find({H, W});
+        if (cc != cached.end() && !tile_built(cc->second.first, cc->second.second)) cc = cached.end();
+        if (cr != cached_rows.end() && !rows_built(cr->second)) cr = cached_rows.end();
+        if (cn != cached_narrow.end() &&  // 0 rows: no choice of them
+            (!tile_built(cn->second[0], cn->second[1]) || (cn->second[2] > 0 && !rows_built(cn->second[2]))))
+            cn = cached_narrow.end();
         if (cc != cached.end()) p->col_shape[{H, W}] = cc->second;
         if (cr != cached_rows.end()) p->row_rows[{H, W}] = cr->second;
         if (cn != cached_narrow.end()) {
