@@ -1526,8 +1526,7 @@ struct SampleWs {
     size_t items_cap = 0;          // in items
     float4* coef = nullptr;        // persistent tables: 40 bytes per pixel pair
     float* dprime = nullptr;       // d / A (response plans)
-    float2* field = nullptr;       // work field when state_out is NULL
-    float2* packed = nullptr;      // fields of the packed classes, one after another (none: they run unpacked)
+    float2* field = nullptr;       // work field when state_out is NULL, and the packed classes' (none: they run unpacked)
     float2* hfield = nullptr;      // 16-bit work field (4 bytes per element)
     bool graphs = true;            // MF_FLAG_GRAPH may capture and instantiate graphs (which allocates)
     bool overlap = true;           // `items` holds a list per size class, so that classes may run side by side
@@ -1616,14 +1615,13 @@ mf_status ensure_sample_workspace(mf_plan p, int pairs, int storage, int form, b
     if (st != MF_OK) return st;
     const size_t field_elems = (size_t)p->total_px * pairs;
     // single-chain problems on the streamed kernels run packed two to a field,
-    // in fields of their own after the work field
-    size_t packed = 0;
+    // in the first one's place of this field whatever state_out is
+    bool packs = false;
     if (pairs == 1 && storage == MF_STORAGE_FP32)
         for (auto& kv : p->classes)
             if (kv.second.size() >= 2 && (form == MF_FORM_STREAMED || !mf::resident_supported(kv.first.first, kv.first.second)))
-                packed += (kv.second.size() + 1) / 2 * (size_t)kv.first.first * kv.first.second;
-    const size_t elems = (need_field ? field_elems : 0) + packed;
-    if (elems && (st = ws(p->field, elems * sizeof(float2), s)) != MF_OK) return st;
+                packs = true;
+    if ((need_field || packs) && (st = ws(p->field, field_elems * sizeof(float2), s)) != MF_OK) return st;
     if (storage != MF_STORAGE_FP32 && (st = ws(p->hfield, field_elems * 4, s)) != MF_OK) return st;
     if (sample_any_persistent(p, form) &&
         (st = ws(p->coef, (size_t)p->total_px / 2 * (sizeof(float4) + sizeof(float2) + sizeof(float4)), s)) != MF_OK)
@@ -1695,7 +1693,6 @@ mf_status sample_impl(mf_plan p, const float* d, const mf_sample_args* g, const 
     ClassStreams cls(p, s, w.overlap && p->classes.size() > 1 && !capturing(s));
     MF_HIP(cls.open());
     mf::ItemDev* items = w.items;
-    float2* pfield = w.packed;
     int n_cls = 0;
     for (auto& kv : p->classes) {
         const int H = kv.first.first, W = kv.first.second;
@@ -1709,7 +1706,7 @@ mf_status sample_impl(mf_plan p, const float* d, const mf_sample_args* g, const 
         // complex field (no imaginary chain computed only to be dropped)
         const int n_pids = (int)kv.second.size();
         const bool packed = form == MF_FORM_STREAMED && g->chains_per_problem == 1 && g->storage == MF_STORAGE_FP32 &&
-                            n_cool == 0 && n_pids >= 2 && pfield && is_pow2(H) && is_pow2(W);
+                            n_cool == 0 && n_pids >= 2 && w.field && is_pow2(H) && is_pow2(W);
         mf::ItemDev* di = nullptr;
         int n_items = 0;
         mf_status st = MF_OK;
@@ -1718,19 +1715,17 @@ mf_status sample_impl(mf_plan p, const float* d, const mf_sample_args* g, const 
             if ((size_t)(items - w.items) + n_items > w.items_cap)
                 return fail(MF_ERR_INVALID_ARG, "internal: items workspace too small");
             di = items;
-            MF_HIP(mf::launch_fill_packed_items(di, p->d_probs, p->d_class_pids + p->class_all.at(kv.first).first, n_pids,
-                                                (int64_t)H * W, s));
-            st = sample_streamed(p, di, n_items, H, W, d, &gm, pfield, sin, samples_out, w.graphs, true, s);
+            MF_HIP(mf::launch_fill_packed_items(di, p->d_probs, p->d_class_pids + p->class_all.at(kv.first).first, n_pids, s));
+            st = sample_streamed(p, di, n_items, H, W, d, &gm, w.field, sin, samples_out, w.graphs, true, s);
             if (st != MF_OK) return st;
             mf::SweepArgs a = base_args(p, H, W);
             a.items = di;
             a.n_items = n_items;
-            a.field = pfield;
+            a.field = w.field;
             a.packed = 1;
             if (state_out) MF_HIP(mf::launch_pack_copy_out(W, H, a, work, s));
             if (g->check_finite) MF_HIP(mf::launch_finite_check(W, H, a, flag, s));
             if (w.overlap) items += n_items;
-            pfield += (size_t)n_items * H * W;
             continue;
         }
         if (form == MF_FORM_PERSISTENT && n_cool == 0) {
@@ -2137,8 +2132,7 @@ mf_status mf_plan_reserve(mf_plan p, const mf_reserve* r) {
         if ((st = ensure_loss_workspace(p, s)) != MF_OK) return st;
     }
     if ((r->calls & MF_RESERVE_SAMPLE) &&
-        ((st = ensure_sample_workspace(p, pairs, r->storage, MF_FORM_AUTO, true, s)) != MF_OK ||
-         (st = ensure_sample_workspace(p, pairs, r->storage, MF_FORM_STREAMED, true, s)) != MF_OK))
+        (st = ensure_sample_workspace(p, pairs, r->storage, MF_FORM_AUTO, true, s)) != MF_OK)
         return st;
     if ((r->calls & MF_RESERVE_SAMPLE) && p->classes.size() > 1) MF_HIP(ClassStreams::prepare(p));
     if ((r->calls & MF_RESERVE_SPECTRUM) && (st = ensure_spectrum_workspace(p, pairs, true, s)) != MF_OK) return st;
@@ -2452,7 +2446,6 @@ mf_status mf_sample(mf_plan p, const float* d, const mf_sample_args* g, const fl
     w.coef = p->coef.as<float4>();
     w.dprime = p->dprime.as<float>();
     w.field = p->field.as<float2>();
-    w.packed = pairs == 1 && w.field ? w.field + (state_out ? 0 : p->total_px) : nullptr;
     w.hfield = p->hfield.as<float2>();
     return sample_impl(p, d, g, state_in, state_out, samples_out, w, s);
 }

@@ -163,8 +163,8 @@ hipError_t launch_band_power(int W, int H, const SweepArgs& a, const float* x, c
 // `local` (a field of the class's items only).
 hipError_t launch_fill_items(ItemDev* out, const ProbDev* probs, const int32_t* pids, int n_pids, int per,
                              int local, int64_t hw, hipStream_t s);
-// Packed work list: item i = (pids[2i], pids[2i+1] or -1, i * hw).
-hipError_t launch_fill_packed_items(ItemDev* out, const ProbDev* probs, const int32_t* pids, int n_pids, int64_t hw,
+// Packed work list: item i = (pids[2i], pids[2i+1] or -1, pix_off of the first).
+hipError_t launch_fill_packed_items(ItemDev* out, const ProbDev* probs, const int32_t* pids, int n_pids,
                                     hipStream_t s);
 // Packed work field from the pair states [problem][1][H][W] (real parts), or
 // zero / dispersed starts; and back (imaginary parts of the states set to 0).

@@ -1267,13 +1267,11 @@ __global__ void fill_items_kernel(ItemDev* out, const ProbDev* probs, const int3
     }
 }
 
-__global__ void fill_packed_items_kernel(ItemDev* out, const ProbDev* probs, const int32_t* pids, int n_pids,
-                                         int64_t hw) {
+__global__ void fill_packed_items_kernel(ItemDev* out, const ProbDev* probs, const int32_t* pids, int n_pids) {
     const int n = (n_pids + 1) / 2;
     for (int i = blockIdx.x * blockDim.x + threadIdx.x; i < n; i += gridDim.x * blockDim.x) {
         const ProbDev pr = probs[pids[2 * i]];
-        out[i] = ItemDev{pids[2 * i], 2 * i + 1 < n_pids ? pids[2 * i + 1] : -1, (int64_t)i * hw, pr.pix_off, pr.tau,
-                         pr.pid};
+        out[i] = ItemDev{pids[2 * i], 2 * i + 1 < n_pids ? pids[2 * i + 1] : -1, pr.pix_off, pr.pix_off, pr.tau, pr.pid};
     }
 }
 
@@ -1710,11 +1708,11 @@ hipError_t launch_fill_items(ItemDev* out, const ProbDev* probs, const int32_t* 
     return hipGetLastError();
 }
 
-hipError_t launch_fill_packed_items(ItemDev* out, const ProbDev* probs, const int32_t* pids, int n_pids, int64_t hw,
+hipError_t launch_fill_packed_items(ItemDev* out, const ProbDev* probs, const int32_t* pids, int n_pids,
                                     hipStream_t s) {
     if (n_pids <= 0) return hipSuccess;
     hipLaunchKernelGGL(fill_packed_items_kernel, elementwise_grid((n_pids + 1) / 2), dim3(256), 0, s, out, probs, pids,
-                       n_pids, hw);
+                       n_pids);
     return hipGetLastError();
 }
 
