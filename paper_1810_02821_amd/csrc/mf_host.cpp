@@ -104,6 +104,61 @@ FlagWords& flag_words() {
     return *w;
 }
 
+// Streams beside the caller's for the size classes of one mf_sample call, with
+// the events that order them after and before the caller's work.
+struct SideStreams {
+    static constexpr int kSides = 3;
+    int device = -1;
+    hipStream_t side[kSides] = {};
+    hipEvent_t fork = nullptr, joined[kSides] = {};
+    void destroy() {
+        if (fork) (void)hipEventDestroy(fork);
+        for (int i = 0; i < kSides; ++i) {
+            if (joined[i]) (void)hipEventDestroy(joined[i]);
+            if (side[i]) (void)hipStreamDestroy(side[i]);
+        }
+    }
+};
+// Sets that destroyed plans leave to later ones, at most kIdle.  Making a set
+// costs a plan's first call and its destruction 90 us (two small classes, create
+// + one call + destroy: 506 us with a set of its own, 416 with another plan's).
+// A set has one owner at a time, and its streams are idle when it changes hands:
+// mf_plan_destroy has freed device memory by then, which waits for the device.
+class SideStreamPool {
+    static constexpr int kIdle = 4;
+    std::mutex m;
+    int n = 0;
+    SideStreams idle[kIdle];
+
+public:
+    SideStreams take(int device) {
+        std::lock_guard<std::mutex> lock(m);
+        for (int i = 0; i < n; ++i)
+            if (idle[i].device == device) {
+                const SideStreams got = idle[i];
+                idle[i] = idle[--n];
+                return got;
+            }
+        SideStreams fresh;
+        fresh.device = device;
+        return fresh;
+    }
+    void give(SideStreams set) {
+        {
+            std::lock_guard<std::mutex> lock(m);
+            if (n < kIdle) {
+                idle[n++] = set;
+                return;
+            }
+        }
+        set.destroy();
+    }
+};
+SideStreamPool& side_stream_pool() {
+    static SideStreamPool* p = new SideStreamPool;  // outlives every plan
+    return *p;
+}
+
 // A device buffer that grows on demand and is freed with the plan.
 struct DevBuf {
     void* p = nullptr;
@@ -168,11 +223,7 @@ struct mf_plan_s {
     };
     std::vector<GraphEntry> graphs;
     hipStream_t cap_stream = nullptr;
-    // streams beside the caller's for the size classes of one mf_sample call,
-    // with the events that order them after and before the caller's work
-    static constexpr int kSides = 3;
-    hipStream_t side[kSides] = {};
-    hipEvent_t fork = nullptr, joined[kSides] = {};
+    SideStreams sides;               // from side_stream_pool(), once a call needs them
     std::vector<float> host_nbar;    // for residual norms
     bool has_response = false;       // some problem has a diagonal A != I
     float* d_rinv = nullptr;         // 1 / A_i per pixel (0 without response), when has_response
@@ -226,11 +277,7 @@ struct mf_plan_s {
             if (g.graph) (void)hipGraphDestroy(g.graph);
         }
         if (cap_stream) (void)hipStreamDestroy(cap_stream);
-        if (fork) (void)hipEventDestroy(fork);
-        for (int i = 0; i < kSides; ++i) {
-            if (joined[i]) (void)hipEventDestroy(joined[i]);
-            if (side[i]) (void)hipStreamDestroy(side[i]);
-        }
+        if (sides.device >= 0) side_stream_pool().give(sides);
     }
 };
 
@@ -1533,48 +1580,54 @@ struct SampleWs {
 };
 
 // The streams of one call's size classes: class i takes the caller's stream or
-// one of the plan's, ordered after the caller's work so far; join() (or the
+// one of the plan's sides, ordered after the caller's work so far; join() (or the
 // destructor, on an error's way out) orders the caller's later work after all.
 struct ClassStreams {
     mf_plan p;
     hipStream_t s;
     bool on;
-    bool used[mf_plan_s::kSides] = {};
+    bool used[SideStreams::kSides] = {};
     ClassStreams(mf_plan plan, hipStream_t stream, bool overlap) : p(plan), s(stream), on(overlap) {}
-    // Create what the plan's classes need (the first call does, or mf_plan_reserve).
+    // Take or create what the plan's classes need (the first call does, or mf_plan_reserve).
     static hipError_t prepare(mf_plan p) {
         hipError_t e = hipSuccess;
-        if (!p->fork) e = hipEventCreateWithFlags(&p->fork, hipEventDisableTiming);
-        for (int k = 0; k < mf_plan_s::kSides && k + 1 < (int)p->classes.size(); ++k) {
-            if (e == hipSuccess && !p->side[k]) e = hipStreamCreateWithFlags(&p->side[k], hipStreamNonBlocking);
-            if (e == hipSuccess && !p->joined[k]) e = hipEventCreateWithFlags(&p->joined[k], hipEventDisableTiming);
+        SideStreams& t = p->sides;
+        if (t.device < 0) {
+            int dev = 0;
+            if ((e = hipGetDevice(&dev)) != hipSuccess) return e;
+            t = side_stream_pool().take(dev);
+        }
+        if (!t.fork) e = hipEventCreateWithFlags(&t.fork, hipEventDisableTiming);
+        for (int k = 0; k < SideStreams::kSides && k + 1 < (int)p->classes.size(); ++k) {
+            if (e == hipSuccess && !t.side[k]) e = hipStreamCreateWithFlags(&t.side[k], hipStreamNonBlocking);
+            if (e == hipSuccess && !t.joined[k]) e = hipEventCreateWithFlags(&t.joined[k], hipEventDisableTiming);
         }
         return e;
     }
     hipError_t open() {
         if (!on) return hipSuccess;
         const hipError_t e = prepare(p);
-        return e == hipSuccess ? hipEventRecord(p->fork, s) : e;
+        return e == hipSuccess ? hipEventRecord(p->sides.fork, s) : e;
     }
     hipError_t of(int i, hipStream_t* out) {
         *out = s;
-        const int k = i % (mf_plan_s::kSides + 1) - 1;
+        const int k = i % (SideStreams::kSides + 1) - 1;
         if (!on || k < 0) return hipSuccess;
         if (!used[k]) {
-            const hipError_t e = hipStreamWaitEvent(p->side[k], p->fork, 0);
+            const hipError_t e = hipStreamWaitEvent(p->sides.side[k], p->sides.fork, 0);
             if (e != hipSuccess) return e;
         }
         used[k] = true;
-        *out = p->side[k];
+        *out = p->sides.side[k];
         return hipSuccess;
     }
     hipError_t join() {
         hipError_t r = hipSuccess;
-        for (int k = 0; k < mf_plan_s::kSides; ++k) {
+        for (int k = 0; k < SideStreams::kSides; ++k) {
             if (!used[k]) continue;
             used[k] = false;
-            hipError_t e = hipEventRecord(p->joined[k], p->side[k]);
-            if (e == hipSuccess) e = hipStreamWaitEvent(s, p->joined[k], 0);
+            hipError_t e = hipEventRecord(p->sides.joined[k], p->sides.side[k]);
+            if (e == hipSuccess) e = hipStreamWaitEvent(s, p->sides.joined[k], 0);
             if (r == hipSuccess) r = e;
         }
         return r;
