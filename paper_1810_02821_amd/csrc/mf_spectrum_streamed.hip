@@ -68,9 +68,15 @@ __device__ __forceinline__ float2 mode_normal(uint32_t e, uint32_t sweep, uint32
 template <int L>
 __global__ __launch_bounds__(PairShape<L>::NTH) void col_pair_kernel(SpectrumStreamArgs a, int W) {
     constexpr int TC = PairShape<L>::TC, NTH = PairShape<L>::NTH, TPC = PairShape<L>::TPC;
+    // twiddles: at 512 rows the table W_L^r (2 L entries before the pass tables),
+    // since the pass tables' 2 KiB more cost the fourth workgroup of a CU (16
+    // fields of 512^2 43.2 against 49.1 us per launch); at 256 rows, where both
+    // leave as many, the pass tables are 1% faster (32 fields 25.5 against 25.7)
+    constexpr bool kBase = L == 512;
+    constexpr int kTw = L < 256 ? 1 : kBase ? L : lds_tw_len<L>();
     // padded exchange layouts from 256 rows (the HBM-side passes) where they
     // keep the resident workgroups per CU, else the XOR swizzle
-    constexpr int kExtra = 8 * lds_tw_len<L>() + (int)(sizeof(double) * 2 * kNB + sizeof(float4) * kNB);  // twiddles and tables beside the tile
+    constexpr int kExtra = 8 * (L < 256 ? lds_tw_len<L>() : kTw) + (int)(sizeof(double) * 2 * kNB + sizeof(float4) * kNB);  // twiddles and tables beside the tile
     constexpr bool kPad = L >= 256 && lds_keeps_blocks(TC * PairShape<L>::SEG * 8 + kExtra,
                                                        TC * PairLayout<L, TC>::SEG * 8 + kExtra);
     constexpr int A1 = kPad ? PairLayout<L, TC>::A1 : -1, AN = kPad ? PairLayout<L, TC>::AN : -1;
@@ -81,8 +87,13 @@ __global__ __launch_bounds__(PairShape<L>::NTH) void col_pair_kernel(SpectrumStr
     __shared__ float2 lds[TC * SEG];
     __shared__ double pw[2][kNB];
     __shared__ float4 coef[kNB];
-    __shared__ float2 twl[L >= 256 ? lds_tw_len<L>() : 1];
-    const TwSplit<lds_tw_lim(L)> tws{a.tw_col, twl};
+    __shared__ float2 twl[kTw];
+    static_assert(L != 512 || 4 * (sizeof lds + sizeof pw + sizeof coef + sizeof twl) <= kLdsPerCU,
+                  "four workgroups per CU");
+    const auto tws = [&] {
+        if constexpr (kBase) return TwBase{twl};
+        else return TwSplit<lds_tw_lim(L)>{a.tw_col, twl};
+    }();
     const unsigned tid = threadIdx.x;
     // tile fastest: an XCD runs neighbouring tiles of one item together, so
     // the cache lines they share meet in its L2
@@ -105,7 +116,9 @@ __global__ __launch_bounds__(PairShape<L>::NTH) void col_pair_kernel(SpectrumStr
     }
     for (unsigned u = tid; u < 2 * kNB; u += NTH) pw[u / kNB][u % kNB] = 0.0;
     for (unsigned u = tid; u < kNB; u += NTH) coef[u] = a.coef[(int64_t)item * kNB + u];
-    if constexpr (L >= 256)
+    if constexpr (kBase)
+        for (unsigned i = tid; i < (unsigned)L; i += NTH) twl[i] = (a.tw_col - 2 * L)[i];
+    else if constexpr (L >= 256)
         stage_twiddles<L, NTH>(twl, a.tw_col, tid);
     __syncthreads();
     const unsigned cid = tid / TPC, lane = tid % TPC;
