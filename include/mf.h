@@ -48,7 +48,10 @@
  * instead.  "host" pointers are read during the call only.
  *
  * Asynchrony: every entry point enqueues its kernels on `stream` (a
- * hipStream_t; NULL is the null stream).  Work lists and cooling levels are
+ * hipStream_t; NULL is the null stream); mf_sample runs the size classes of a
+ * plan side by side, on streams of the library's that start after the work
+ * queued on `stream` and end before what the caller queues next (while `stream`
+ * is being captured, one after another on it).  Work lists and cooling levels are
  * built on the device or passed in kernel arguments, so mf_sample,
  * mf_sample_spectrum, mf_shear_sample (check_finite = 0), mf_wiener and
  * mf_wiener_backward (tol <= 0, info NULL), mf_wiener_backward_unrolled,
@@ -150,7 +153,8 @@ enum {
     MF_FLAG_AUTOTUNE = 1,      /* time the column-tile shapes and the fused row kernel's rows per workgroup
                                   of each streamed size class (sides >= 256) at plan creation and keep the
                                   fastest of each; with MF_TUNE_CACHE=<file> in the environment the
-                                  choices are read from / appended to that file */
+                                  choices are read from / appended to that file (lines that name a
+                                  shape this library does not have are passed over) */
     MF_FLAG_GRAPH = 2,         /* capture the streamed sweep loops of each size class (mf_sample,
                                   mf_sample_spectrum, mf_shear_wiener, mf_shear_sample) as HIP graphs,
                                   once per launch configuration (pointers, counts, seeds, sweep range,
@@ -459,10 +463,11 @@ mf_status mf_plan_row_shape(mf_plan plan, int32_t H, int32_t W, int32_t* rows);
 
 /* Shapes of the size class H x W for launches too small to fill the GPU: a
  * launch whose grid in the shapes above would have fewer workgroups than the
- * GPU has compute units (256; a single Wiener solve or adjoint of a 256^2 or
- * 512^2 image, a few chains) uses these instead.  Under MF_FLAG_AUTOTUNE they
- * are timed on one work item; otherwise they are the candidates with the most
- * workgroups.  *cols x *threads: column tile; *rows: rows per workgroup of the
+ * GPU has compute units (256; a few chains of a 256^2 or 512^2 image) uses these
+ * instead.  (Wiener solves and adjoints with both sides powers of two from 256
+ * run on kernels of their own, whose shapes are fixed.)  Under MF_FLAG_AUTOTUNE
+ * they are timed on one work item; otherwise they are the candidates with the
+ * most workgroups.  *cols x *threads: column tile; *rows: rows per workgroup of the
  * fused row kernel (0 where none runs).  Every shape computes the same values
  * bit for bit.  MF_ERR_INVALID_ARG if the plan has no problem of that size. */
 mf_status mf_plan_narrow_shape(mf_plan plan, int32_t H, int32_t W, int32_t* cols, int32_t* threads,

@@ -1147,7 +1147,7 @@ bool solve_resident(mf_plan p, int H, int W) {
 }
 
 // Run the deterministic solve of every problem and write the real result to
-// `out` (concatenated).  The streamed classes also leave it in the field buffer.
+// `out` (concatenated).
 mf_status run_solve(mf_plan p, const float* src, int src_kind, const mf_schedule* sch, const float* s_init,
                     float* out, mf_info* info_out, hipStream_t s) {
     mf_status st = validate_schedule(sch);

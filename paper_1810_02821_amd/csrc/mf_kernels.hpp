@@ -175,8 +175,8 @@ hipError_t launch_pack_copy_out(int W, int H, const SweepArgs& a, float2* state_
 hipError_t launch_col_pack(int W, int H, const SweepArgs& a, hipStream_t s);
 // Zero n 4-byte words (a kernel, so that captured graphs hold no memset node).
 hipError_t launch_zero_words(void* p, int64_t n_words, hipStream_t s);
-// flag[0] = min(flag[0], problem) for every item whose field (H x W elements
-// of the given storage) holds a NaN or an infinity.
+// Report to `flag` every problem of whose items a field (H x W elements of the
+// given storage) holds a NaN or an infinity.
 hipError_t launch_finite_check(int W, int H, const SweepArgs& a, FiniteFlag flag, hipStream_t s);
 // Loss terms of a band-spectrum problem at s (one item per problem, d and s
 // concatenated, d already divided by the response): per item FP64 partial

@@ -132,7 +132,7 @@ struct ShearStep {
 // since a Philox call's two modes sit in neighbouring lanes.  VALU-bound: about
 // 3,400 instructions per wave and sweep at 128^2 (4,900 with Z and eta exchanged
 // for the mirror and the coefficients evaluated three times), 88% of the issue
-// rate; 512 chains x 80 sweeps 5.23 -> 4.12 ms.
+// rate; 512 chains x 80 sweeps 5.23 -> 4.06 ms.
 template <int N>
 __device__ __forceinline__ void harmonic_shear(float2 (&v)[16], float2* lds, float2* sz, const ShearArgs& a, const ProbDev& pr,
                                                float T, uint32_t sweep, int chain, unsigned tid, bool times_d) {

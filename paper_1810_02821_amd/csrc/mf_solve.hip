@@ -25,7 +25,9 @@
 // 21.0 -> 11.2 ms.  With 16 values per thread 32^2 and 64^2 took 4.2 us (half
 // a wave and two waves, one after the other's latencies).  At 128^2 the VALU
 // issues 1,440 instructions per wave and sweep, 72% of the time at two waves
-// per SIMD; the rest is latency (LDS exchanges behind block barriers).
+// per SIMD; the rest is latency (LDS exchanges behind block barriers).  A batch
+// lasts as long as its slowest image (those 256: 860 to 1,620 sweeps, mean 1,089),
+// so over its whole run the VALU issues 51% of the time.
 #include "mf_device.hpp"
 #include "mf_resident.hpp"
 #include "mf_resident_fft.hpp"

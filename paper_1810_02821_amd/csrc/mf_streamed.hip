@@ -394,7 +394,7 @@ void row_kernel_f(SweepArgs a, int H) {
     __shared__ float2 lds[ROWS * LP];
     // up to 512 points the table W_L^r (2 L entries before the pass tables) costs
     // less than the pass tables, which are twice its size
-    // (128 fields of 256^2 23.2 against 23.8 us, 16 of 512^2 24.9 against 25.6)
+    // (64 fields of 256^2 23.2 against 23.8 us, 16 of 512^2 24.9 against 25.6)
     constexpr bool kBase = L <= 512;
     __shared__ float2 twl[kBase ? L : lds_tw_len<L>()];
     static_assert(ROWS * LP >= kThreads, "residual partials fit in the rows");

@@ -18,7 +18,13 @@ constexpr int middle_radix() { return middle_radix_of(L); }
 // coalesced load per twiddle.  All tables in LDS cost resident workgroups, none
 // there exposes L2's latency in the middle passes (us per sweep kernel, FP32,
 // none / these / all in LDS; 2048^2 x 8 and 1024^2 x 16 fields: rows 213 / 185
-// / 298 and 91 / 75 / 98, columns 249 / 247 / - and 80 / 76 / 83).
+// / 298 and 91 / 75 / 98, columns 249 / 247 / - and 80 / 76 / 83).  Up to 512
+// points three kernels keep the one table W_L^r in LDS, half as large, and say
+// why; in the others it is within 2% of these tables either way (us per launch,
+// W_L^r / these: col_kernel_f 64 fields of 256^2 21.0 / 21.3 and 16 of 512^2 24.8
+// / 24.8, col_pack_kernel 40.0 / 40.2 and 43.9 / 43.9, 419 and 192 packed fields
+// 216 / 219 and 369 / 365, shear_row_kernel_f 64 chains of 256^2 26.7 / 27.2 and
+// 32 of 512^2 50.0 / 49.7).
 constexpr int lds_tw_lim(int L) { return L >= 1024 && is_pow2(L) ? 16 : L == 512 ? 32 : L == 256 ? 16 : L; }
 // Copy them (visible after the caller's next barrier).
 template <int L, int NTH, int LIM = lds_tw_lim(L)>
